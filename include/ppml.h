@@ -148,7 +148,7 @@ typedef struct ppml_grid ppml_grid;
 
 /* Bytes of device memory the caller must provide for the state
  * ((3+ndim) * cells * sizeof(storage type)) and for the scratch area (the
- * Eulerian-stage output, the control block and reduction partials).
+ * Eulerian-stage output, the control block and the CFL maxima).
  * Returns 0 for an invalid descriptor. */
 size_t ppml_state_bytes(const ppml_desc *d);
 size_t ppml_scratch_bytes(const ppml_desc *d);
@@ -308,7 +308,7 @@ int ppml_batch_destroy(ppml_batch *b);
  * of the state already on the device, ppml_step and ppml_get_time do, with
  * the same kernels and the same results, but allocates nothing: no device or
  * host memory, no host object, no graph.  The grid's work area (the
- * Eulerian-stage output, the control block and the totals partials: the
+ * Eulerian-stage output, the control block and the CFL maxima: the
  * ppml_scratch_bytes of the descriptor) lies in a fixed area inside the
  * library, PPML_NOALLOC_SCRATCH_BYTES per GPU, held from the first call on
  * that GPU until the process ends.

@@ -156,8 +156,17 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 // Totals reduction: fixed number of blocks so the summation order is fixed.
 int totals_blocks(long long n) { return (int)std::min<long long>(1024, (n + 4095) / 4096 > 0 ? (n + 4095) / 4096 : 1); }
 
+// Bytes behind the control block for the maxima slots (two sets), and how many
+// slots a set has there: about one per 43 work groups of 256 cells, at most
+// one per lane of the wave that folds them.
+size_t maxima_bytes(long long n) { return align_up((size_t)totals_blocks(n) * 6 * sizeof(double)); }
+int maxima_slots(long long n)
+{
+    return (int)std::min<size_t>(MSLOT_MAX, maxima_bytes(n) / (2 * MSLOT_BYTES));
+}
+
 struct ScratchLayout {
-    size_t half, ctrl, partial, totals;
+    size_t half, ctrl, maxima, totals;
     // self-gravity: padded potential, two work arrays, sine matrices,
     // eigenvalue factors, moment partials, shell terms of the outer layer
     size_t phi, wx, wy, sx, sy, sz, fx, fy, fz, gpart, gedge;
@@ -173,9 +182,9 @@ ScratchLayout layout(const ppml_desc *d)
     L.half = 0;
     size_t sz = align_up((size_t)nfields(d) * (size_t)ncells(d) * elem(d));
     L.ctrl = sz;
-    sz += align_up(sizeof(Ctrl));
-    L.partial = sz;
-    sz += align_up((size_t)totals_blocks(ncells(d)) * 6 * sizeof(double));
+    sz += CTRL_BYTES;
+    L.maxima = sz;
+    sz += maxima_bytes(ncells(d));
     L.totals = sz;
     sz += align_up(8 * sizeof(double));
     L.phi = L.wx = L.wy = L.sx = L.sy = L.sz = L.fx = L.fy = L.fz = L.gpart = L.gedge = 0;
@@ -220,7 +229,6 @@ struct ppml_grid {
     void *state;
     void *half;
     Ctrl *ctrl;
-    double *partial;
     double *totals;
     bool in_batch;         // admitted to a batch: stepped only by the batch
     hipStream_t bstream;   // that batch's stream (the batch kernels write the state there)
@@ -243,11 +251,11 @@ namespace {
 template <typename T> void launch_speeds(ppml_grid *g)
 {
     const T *U = (const T *)g->state;
-    int nb = (int)std::min<long long>(4096, (g->gp.ncell + 255) / 256);
+    const int nb = (int)std::min<long long>(2048, (g->gp.ncell + SPEED_THREADS - 1) / SPEED_THREADS);
     switch (g->d.ndim) {
-    case 1: k_speeds<T, 1><<<nb, 256, 0, g->stream>>>(U, g->gp, g->ctrl); break;
-    case 2: k_speeds<T, 2><<<nb, 256, 0, g->stream>>>(U, g->gp, g->ctrl); break;
-    default: k_speeds<T, 3><<<nb, 256, 0, g->stream>>>(U, g->gp, g->ctrl); break;
+    case 1: k_speeds<T, 1><<<nb, SPEED_THREADS, 0, g->stream>>>(U, g->gp, g->ctrl); break;
+    case 2: k_speeds<T, 2><<<nb, SPEED_THREADS, 0, g->stream>>>(U, g->gp, g->ctrl); break;
+    default: k_speeds<T, 3><<<nb, SPEED_THREADS, 0, g->stream>>>(U, g->gp, g->ctrl); break;
     }
 }
 
@@ -398,8 +406,11 @@ template <typename T> void launch_totals(ppml_grid *g, double mean_cells)
     const long long N = g->gp.ncell;
     int nb = totals_blocks(N);
     long long chunk = (N + nb - 1) / nb;
-    k_totals_partial<T><<<nb, TOT_THREADS, 0, g->stream>>>((const T *)g->state, N, nfields(&g->d), chunk, g->partial);
-    k_totals_final<<<1, TOT_THREADS, 0, g->stream>>>(g->partial, nb, nfields(&g->d), g->d.ndim, g->totals, g->ctrl,
+    // the partial sums go to the stage output's area (48 bytes per 4096 cells,
+    // at least 256 bytes), which holds nothing between steps
+    double *partial = (double *)g->half;
+    k_totals_partial<T><<<nb, TOT_THREADS, 0, g->stream>>>((const T *)g->state, N, nfields(&g->d), chunk, partial);
+    k_totals_final<<<1, TOT_THREADS, 0, g->stream>>>(partial, nb, nfields(&g->d), g->d.ndim, g->totals, g->ctrl,
                                                       mean_cells);
 }
 
@@ -432,7 +443,7 @@ int settle(ppml_grid *g)
 // the host.
 int finish_set_async(ppml_grid *g, double t, double rho_mean0)
 {
-    k_ctrl_reset<<<1, 1, 0, g->stream>>>(g->ctrl, t, rho_mean0);
+    k_ctrl_reset<<<1, 2 * MSLOT_MAX, 0, g->stream>>>(g->ctrl, g->gp.mslots, t, rho_mean0);
     HIPCHK(hipGetLastError());
     if (g->d.prec == PPML_FP64) {
         launch_totals<double>(g, rho_mean0 > 0.0 ? 0.0 : (double)g->gp.ncell);
@@ -605,7 +616,6 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
     char *s = (char *)scratch_dev;
     g->half = s + L.half;
     g->ctrl = (Ctrl *)(s + L.ctrl);
-    g->partial = (double *)(s + L.partial);
     g->totals = (double *)(s + L.totals);
     GridParams &gp = g->gp;
     memset(&gp, 0, sizeof gp);
@@ -621,6 +631,7 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
         if (a < d->ndim && gp.h[a] < hmin) hmin = gp.h[a];
     }
     gp.ncell = ncells(d);
+    gp.mslots = maxima_slots(gp.ncell);
     gp.gamma = d->gamma;
     if (d->flags & PPML_FLAG_ISOTHERMAL) {
         gp.pa = d->iso_cs * d->iso_cs;
@@ -948,7 +959,7 @@ int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop)
 }  // extern "C"
 
 // Work area of ppml_step_noalloc: the Eulerian-stage output, the control block
-// and the totals partials of one grid, one copy per GPU the library runs on,
+// and the CFL maxima of one grid, one copy per GPU the library runs on,
 // held until the process ends.  Host code never passes the array's name to a
 // kernel or a copy (in host code it is only a stand-in for the device
 // symbol): its device address comes from hipGetSymbolAddress, once per device.
@@ -1005,7 +1016,7 @@ int ppml_step_noalloc(const ppml_desc *d, void *state_dev, double rho_mean0, dou
     if ((rc = init_grid(&g, d, state_dev, area, hip_stream))) return rc;
     init_chunks(&g);
     // every value of the work area that a step reads is written first: the
-    // control block by the reset, the maxima slots, the mean density and the
+    // control block and the maxima slots by the reset, the mean density and the
     // partials by the kernels below, the stage output by the Eulerian kernel
     if ((rc = finish_set_async(&g, t0, rho_mean0))) return rc;
     if (nsteps > 0) {
@@ -1049,11 +1060,12 @@ int ppml_max_speeds(ppml_grid *g, double *vmax, double *cmax)
     if (rc) return rc;
     if ((rc = settle(g))) return rc;
     Ctrl c;
+    k_fold_max<<<1, 64, 0, g->stream>>>(g->ctrl, g->gp.mslots);
+    HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(&c, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, g->stream));
     HIPCHK(hipStreamSynchronize(g->stream));
-    int slot = c.slot_cur;
     double v, cs;
-    unsigned long long vb = c.vmax_bits[slot], cb = c.cmax_bits[slot];
+    unsigned long long vb = c.vmax_bits, cb = c.cmax_bits;
     memcpy(&v, &vb, sizeof v);
     memcpy(&cs, &cb, sizeof cs);
     if (vmax) *vmax = v;

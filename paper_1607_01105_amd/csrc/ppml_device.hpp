@@ -42,6 +42,7 @@ struct GridParams {
     int tiles[3];  // work-group tiles along x, y and z chunks of the stage kernels
     int cz;        // planes per z chunk (3-D)
     int any_inflow;  // some face has an inflow boundary (states in Ctrl::inflow)
+    int mslots;      // slots the CFL maxima of a state are spread over (see max_slot)
     int self_grav;   // 1: the force includes the gradient of the self-gravity potential
     const void *phi; // that potential (storage type): interior cells plus a one-cell
                      // shell, C order [k+1][j+1][i+1] with extents n+2
@@ -50,27 +51,44 @@ struct GridParams {
 // Device control block of one grid (lives in the scratch area).  Every
 // field is written by one thread of one kernel and read by the next kernel
 // on the stream, never by another work group of the kernel that writes it:
-// the Eulerian kernel reads slot_cur, t and the run parameters and writes
-// tau, slot_l and the other maxima slot; the Lagrangian kernel reads tau and
-// slot_l and writes t, the step counters and slot_cur.
+// the Eulerian kernel reads slot_cur, t, the run parameters and the current
+// maxima and writes tau, slot_l and zeros over the other maxima; the
+// Lagrangian kernel reads tau and slot_l and writes t, the step counters,
+// slot_cur and the new state's maxima.
 struct Ctrl {
     double t;             // simulation time
     double tau;           // time step of the step in flight (0: no-op step)
     double rho_mean0;     // FP64 initial mean density (vacuum reference)
     double dt_last;       // last time step taken
-    unsigned long long vmax_bits[2];  // max |v| of a state, as FP64 bits (two slots)
-    unsigned long long cmax_bits[2];  // max c, as FP64 bits
+    unsigned long long vmax_bits;  // max |v| of the state as FP64 bits, folded from its slots for the host
+    unsigned long long cmax_bits;  // max c likewise
     long long steps;      // steps taken
     long long steps_left; // steps the current run may still take
     double dt_fixed;      // run parameter: > 0 fixed time step
     double t_stop;        // run parameter: > 0 end time
     int err;              // sticky error word (bit 0: non-physical state)
-    int slot_cur;         // slot holding the maxima of the current state
+    int slot_cur;         // set of maxima slots of the current state (0 or 1)
     int slot_l;           // slot_cur of the step in flight (for the Lagrangian kernel)
     int pad;
     double inflow[6][6];  // conserved ghost state of inflow face 2*axis+side (set once)
     double mom[8];        // mass and second moments of the state (self-gravity boundary values)
 };
+
+// CFL maxima of a state (FP64 bits of max |v| and max c).  They lie behind the
+// control block, in two sets that alternate from step to step, each spread
+// over GridParams::mslots slots of 64 bytes: a work group adds its maxima to
+// the slot of its index modulo mslots, and the next step folds the slots.
+// One pair for all groups serialised the atomics at 11.6 ns each, measured on
+// 32768 of them, which was the longest part of a Lagrangian launch on small
+// grids (2-D 256^2 FP32, two atomics per wave: 30.3 us of a 36 us step) and
+// the tail of every large one.
+constexpr size_t CTRL_BYTES = (sizeof(Ctrl) + 255) / 256 * 256;
+constexpr size_t MSLOT_BYTES = 64;
+constexpr int MSLOT_MAX = 64;  // the fold reads one slot per lane of a wave
+__host__ __device__ __forceinline__ unsigned long long *max_slot(Ctrl *c, int mslots, int set, int i)
+{
+    return (unsigned long long *)((char *)c + CTRL_BYTES + (size_t)(set * mslots + i) * MSLOT_BYTES);
+}
 
 #ifdef PPML_EXACT
 #define PPML_DIV(a, b, inv_b) ((a) / (b))
@@ -101,6 +119,22 @@ __device__ __forceinline__ double med0(double a, double b)
     return __builtin_fmax(__builtin_fmin(a, b), __builtin_fmin(__builtin_fmax(a, b), 0.0));
 }
 __device__ __forceinline__ double dmin(double a, double b) { return __builtin_fmin(a, b); }
+
+// A value that is the same in every lane, held in scalar registers.  Results
+// of floating-point conversions and arithmetic land in vector registers even
+// where every lane holds the same value; the stage kernels' parameters so
+// derived are moved back, which frees the register each would hold per lane.
+__device__ __forceinline__ float uniform(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ double uniform(double x)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
 
 // Reciprocal and reciprocal square root of a positive normal value for the
 // product build: FP32 the hardware estimates (about 1 ulp, as the build's
@@ -495,18 +529,62 @@ __device__ __forceinline__ void self_gravity_grad(const GridParams &gp, int i, i
     g[2] = g[2] + PPML_DIV((double)ph[b + pp] - (double)ph[b - pp], h2, ih2);
 }
 
+// Wave-wide maximum of unsigned 64-bit values over DPP (no LDS round trips),
+// as a wave-uniform value; every lane must be active.
+template <int CTRL_> __device__ __forceinline__ unsigned long long dpp_umax(unsigned long long v)
+{
+    const int lo = (int)(unsigned)v, hi = (int)(unsigned)(v >> 32);
+    const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL_, 0xF, 0xF, false);
+    const unsigned h = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL_, 0xF, 0xF, false);
+    const unsigned long long w = ((unsigned long long)h << 32) | l;
+    return w > v ? w : v;
+}
+__device__ __forceinline__ unsigned long long wave_umax(unsigned long long v)
+{
+    v = dpp_umax<0x111>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds the row's maximum
+    v = dpp_umax<0x112>(v);
+    v = dpp_umax<0x114>(v);
+    v = dpp_umax<0x118>(v);
+    v = dpp_umax<0x142>(v);  // row_bcast 15, 31: lane 63 holds the wave's
+    v = dpp_umax<0x143>(v);
+    const unsigned l = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+    const unsigned h = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
+    return ((unsigned long long)h << 32) | l;
+}
+
+// Maxima of |v| and c of the current state, folded from its slots (positive
+// FP64 values compare as their bits do; a NaN's bits exceed every number's, so
+// that it reaches the time step).  Every lane of the wave must be active.
+__device__ __forceinline__ void fold_max(Ctrl *c, int mslots, int set, unsigned long long &vm, unsigned long long &cm)
+{
+    const int ln = threadIdx.x & 63;
+    unsigned long long v[2] = {0, 0}, s[2] = {0, 0};
+    if (ln < mslots) {
+        // both sets, so that the loads do not wait for the control block's
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            const unsigned long long *p = max_slot(c, mslots, q, ln);
+            v[q] = p[0];
+            s[q] = p[1];
+        }
+    }
+    vm = wave_umax(set ? v[1] : v[0]);
+    cm = wave_umax(set ? s[1] : s[0]);
+}
+
 // Time step of the next step (Sec. 2.1 CFL condition, or the fixed step),
 // clipped to end at t_stop; 0 when the run has no steps left.
-__device__ __forceinline__ double compute_tau(const Ctrl *c, const GridParams &gp)
+__device__ __forceinline__ double compute_tau(Ctrl *c, const GridParams &gp)
 {
+    unsigned long long vb, cb;
+    fold_max(c, gp.mslots, c->slot_cur, vb, cb);
     if (c->steps_left <= 0) return 0.0;
     double tau;
     if (c->dt_fixed > 0.0) {
         tau = c->dt_fixed;
     } else {
-        const int s = c->slot_cur;
-        double vm = __longlong_as_double((long long)c->vmax_bits[s]);
-        double cm = __longlong_as_double((long long)c->cmax_bits[s]);
+        double vm = __longlong_as_double((long long)vb);
+        double cm = __longlong_as_double((long long)cb);
         tau = gp.cfl_hmin / (vm + cm);
     }
     if (c->t_stop > 0.0) {

@@ -105,16 +105,21 @@ template <typename T> __global__ void k_to_double(const T *__restrict__ src, dou
         dst[c] = (double)src[c];
 }
 
-// Control block of a freshly set state: time t, vacuum reference density
-// rho_mean0 (<= 0: left for the totals kernel to fill in).
-__global__ void k_ctrl_reset(Ctrl *ctrl, double t, double rho_mean0)
+// Control block and maxima slots of a freshly set state: time t, vacuum
+// reference density rho_mean0 (<= 0: left for the totals kernel to fill in).
+__global__ __launch_bounds__(2 * MSLOT_MAX) void k_ctrl_reset(Ctrl *ctrl, int mslots, double t, double rho_mean0)
 {
+    if ((int)threadIdx.x < 2 * mslots) {
+        unsigned long long *p = max_slot(ctrl, mslots, 0, threadIdx.x);
+        p[0] = 0ull;
+        p[1] = 0ull;
+    }
+    if (threadIdx.x != 0) return;
     ctrl->t = t;
     ctrl->rho_mean0 = rho_mean0 > 0.0 ? rho_mean0 : 0.0;
     ctrl->tau = 0.0;
     ctrl->dt_last = 0.0;
-    ctrl->vmax_bits[0] = ctrl->vmax_bits[1] = 0ull;
-    ctrl->cmax_bits[0] = ctrl->cmax_bits[1] = 0ull;
+    ctrl->vmax_bits = ctrl->cmax_bits = 0ull;
     ctrl->steps = 0;
     ctrl->steps_left = 0;
     ctrl->dt_fixed = 0.0;
@@ -165,24 +170,99 @@ __device__ __forceinline__ void cell_speeds(T r, T mx, T my, T mz, T e, T prho, 
 #endif
 }
 
-__device__ __forceinline__ void publish_max(Ctrl *ctrl, int slot, double v, double c)
+// Total-energy correction (Sec. 2.4) of a cell's conserved densities after the
+// Lagrangian stage, FP64 arithmetic; thr: the vacuum density.
+template <typename T, int NDIM> __device__ __forceinline__ void energy_correction(T (&fn)[3 + NDIM], double thr)
 {
+    const double r = (double)fn[0];
+    double mx = (double)fn[1];
+    double my = NDIM >= 2 ? (double)fn[2] : 0.0;
+    double mz = NDIM >= 3 ? (double)fn[3] : 0.0;
+    const double Et = (double)fn[NDIM + 1];
+    double e = (double)fn[NDIM + 2];
+    if (r < thr) {
+        const double E = Et / r, eps = e / r;
+        const double w = __builtin_sqrt(mx * mx + my * my + mz * mz) / r;
+        if (E > eps && w > 0.0) {
+            const double sc = __builtin_sqrt(2.0 * (E - eps)) / w;
+            fn[1] = (T)(mx * sc);
+            if constexpr (NDIM >= 2) fn[2] = (T)(my * sc);
+            if constexpr (NDIM >= 3) fn[3] = (T)(mz * sc);
+        } else {
+            fn[1] = T(0);
+            if constexpr (NDIM >= 2) fn[2] = T(0);
+            if constexpr (NDIM >= 3) fn[3] = T(0);
+            fn[NDIM + 2] = (T)Et;
+        }
+    } else {
+#ifdef PPML_EXACT
+        const double kin = (mx * mx + my * my + mz * mz) / (2.0 * r);
+#else
+        const double kin = (mx * mx + my * my + mz * mz) * (0.5 * fast_rcp(r));
+#endif
+        const double d = Et - kin;
+        if (d > 0.0) fn[NDIM + 2] = (T)d;
+    }
+}
+
+// A cell that a step left non-physical or non-finite.
+template <typename T> __device__ __forceinline__ bool bad_cell(T r, T Et, T e, T v, T c)
+{
+    return !(r > T(0)) || !(e > T(0)) || !(v == v) || !(c == c) || __builtin_isinf(v) || __builtin_isinf(Et);
+}
+
+// Adds the work group's maxima of |v| and c to slot i of a set: the waves'
+// maxima through LDS (red: 2 NT / 64 values that no thread still reads), then
+// one atomic per quantity and group.
+template <int NT, typename T>
+__device__ __forceinline__ void publish_max(Ctrl *ctrl, int mslots, int set, int i, T v, T c, T *red)
+{
+    constexpr int NW = NT / 64;
     v = wave_max(v);
     c = wave_max(c);
-    if ((threadIdx.x & 63) == 0) {
-        atomicMax(&ctrl->vmax_bits[slot], (unsigned long long)__double_as_longlong(v));
-        atomicMax(&ctrl->cmax_bits[slot], (unsigned long long)__double_as_longlong(c));
+    if constexpr (NW > 1) {
+        const int w = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) {
+            red[w] = v;
+            red[NW + w] = c;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            v = red[threadIdx.x * NW];
+#pragma unroll
+            for (int q = 1; q < NW; q++) {
+                const T u = red[threadIdx.x * NW + q];
+                v = v > u ? v : u;
+            }
+        }
+    } else if (threadIdx.x == 1) {
+        v = c;
+    }
+    if (threadIdx.x < 2)
+        atomicMax(max_slot(ctrl, mslots, set, i) + threadIdx.x, (unsigned long long)__double_as_longlong((double)v));
+}
+
+// The current maxima into the control block, for the host.
+__global__ __launch_bounds__(64) void k_fold_max(Ctrl *ctrl, int mslots)
+{
+    unsigned long long v, c;
+    fold_max(ctrl, mslots, ctrl->slot_cur, v, c);
+    if (threadIdx.x == 0) {
+        ctrl->vmax_bits = v;
+        ctrl->cmax_bits = c;
     }
 }
 
 // Maxima of |v| and c over the state into the current slot (first step).
+constexpr int SPEED_THREADS = 256;
 template <typename T, int NDIM>
-__global__ void k_speeds(const T *__restrict__ U, GridParams gp, Ctrl *ctrl)
+__global__ __launch_bounds__(SPEED_THREADS) void k_speeds(const T *__restrict__ U, GridParams gp, Ctrl *ctrl)
 {
-    const int slot = ctrl->slot_cur;
+    __shared__ T red[2 * SPEED_THREADS / 64];
+    const int set = ctrl->slot_cur;
     const long long N = gp.ncell;
     const T gam = (T)gp.gs, gm1 = (T)gp.pb, prho = (T)gp.pa;
-    double vm = 0.0, cm = 0.0;
+    T vm = T(0), cm = T(0);
     for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (long long)gridDim.x * blockDim.x) {
         T r = U[c];
         T mx = U[N + c];
@@ -191,10 +271,10 @@ __global__ void k_speeds(const T *__restrict__ U, GridParams gp, Ctrl *ctrl)
         T e = U[(2 + NDIM) * N + c];
         T v, cs;
         cell_speeds<T, NDIM>(r, mx, my, mz, e, prho, gam, gm1, v, cs);
-        vm = vm > (double)v ? vm : (double)v;
-        cm = cm > (double)cs ? cm : (double)cs;
+        vm = vm > v ? vm : v;
+        cm = cm > cs ? cm : cs;
     }
-    publish_max(ctrl, slot, vm, cm);
+    publish_max<SPEED_THREADS>(ctrl, gp.mslots, set, (int)(blockIdx.x % gp.mslots), vm, cm, red);
 }
 
 // Deterministic FP64 totals: fixed per-block ranges and fixed tree order.
@@ -258,6 +338,7 @@ template <typename T, int NDIM, int TX, int TY, int XF = 0>
 __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restrict__ Wst, const GridParams &gp,
                                            Ctrl *ctrl, const int bx, const int by, const int bz, const bool lead)
 {
+    // lead: the work group that publishes the step
     constexpr int NT = TX * TY;
     constexpr int NF = 3 + NDIM;
     constexpr int HX = GH;
@@ -320,27 +401,31 @@ __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restric
     const int nx = gp.n[0], ny = gp.n[1], nz = gp.n[2];
     const long long N = gp.ncell;
 
-    const double tau_d = compute_tau(ctrl, gp);
+    const double tau_d = uniform(compute_tau(ctrl, gp));
     if (lead) {
         // publish the step for the Lagrangian kernel; a no-op step (tau = 0)
-        // leaves the state, its maxima slot and the time unchanged
+        // leaves the state, its maxima and the time unchanged
         const int s = ctrl->slot_cur;
-        ctrl->slot_l = s;
-        ctrl->tau = tau_d > 0.0 ? tau_d : 0.0;
-        if (tau_d > 0.0) {
-            ctrl->vmax_bits[s ^ 1] = 0ull;
-            ctrl->cmax_bits[s ^ 1] = 0ull;
+        if (tid == 0) {
+            ctrl->slot_l = s;
+            ctrl->tau = tau_d > 0.0 ? tau_d : 0.0;
+        }
+        if (tau_d > 0.0 && tid < gp.mslots) {
+            unsigned long long *p = max_slot(ctrl, gp.mslots, s ^ 1, tid);
+            p[0] = 0ull;
+            p[1] = 0ull;
         }
     }
     if (!(tau_d > 0.0)) return;
 
-    const T gam = (T)gp.gs;
-    const T gm1 = (T)gp.pb;
-    const T prho = (T)gp.pa;
-    const T tau = (T)tau_d;
-    const T hx = (T)gp.h[0], hy = (T)gp.h[1], hz = (T)gp.h[2];
-    const T ihx = (T)gp.inv_h[0], ihy = (T)gp.inv_h[1], ihz = (T)gp.inv_h[2];
-    const T tohx = (T)(tau_d * gp.inv_h[0]), tohy = (T)(tau_d * gp.inv_h[1]), tohz = (T)(tau_d * gp.inv_h[2]);
+    const T gam = uniform((T)gp.gs);
+    const T gm1 = uniform((T)gp.pb);
+    const T prho = uniform((T)gp.pa);
+    const T tau = uniform((T)tau_d);
+    const T hx = uniform((T)gp.h[0]), hy = uniform((T)gp.h[1]), hz = uniform((T)gp.h[2]);
+    const T ihx = uniform((T)gp.inv_h[0]), ihy = uniform((T)gp.inv_h[1]), ihz = uniform((T)gp.inv_h[2]);
+    const T tohx = uniform((T)(tau_d * gp.inv_h[0])), tohy = uniform((T)(tau_d * gp.inv_h[1]));
+    const T tohz = uniform((T)(tau_d * gp.inv_h[2]));
     (void)hz;
     (void)ihz;
     (void)tohz;
@@ -467,7 +552,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(euler_wa
 {
     int bx, by, bz;
     block_tile(gp, bx, by, bz);
-    euler_body<T, NDIM, TX, TY, XF>(U, Wst, gp, ctrl, bx, by, bz, blockIdx.x == 0 && threadIdx.x == 0);
+    euler_body<T, NDIM, TX, TY, XF>(U, Wst, gp, ctrl, bx, by, bz, blockIdx.x == 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -489,7 +574,8 @@ template <typename T> __device__ __forceinline__ T tmpl3(T vp, T vm, T ctr)
 
 template <typename T, int NDIM, int TX, int TY, int G>
 __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restrict__ U, const GridParams &gp,
-                                          Ctrl *ctrl, const int bx, const int by, const int bz, const bool lead)
+                                          Ctrl *ctrl, const int bx, const int by, const int bz, const bool lead,
+                                          const int slot_i)
 {
     constexpr int NT = TX * TY;
     constexpr int NF = 3 + NDIM;
@@ -548,15 +634,16 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
     const int x0 = bx * TX, y0 = by * TY;
     const int nx = gp.n[0], ny = gp.n[1], nz = gp.n[2];
     const long long N = gp.ncell;
-    const T gam = (T)gp.gs;
-    const T gm1 = (T)gp.pb;
-    const T prho = (T)gp.pa;
-    const T tau = (T)tau_d;
-    const T hx = (T)gp.h[0], hy = (T)gp.h[1], hz = (T)gp.h[2];
-    const T ihx = (T)gp.inv_h[0], ihy = (T)gp.inv_h[1], ihz = (T)gp.inv_h[2];
-    const T tohx = (T)(tau_d * gp.inv_h[0]), tohy = (T)(tau_d * gp.inv_h[1]), tohz = (T)(tau_d * gp.inv_h[2]);
+    const T gam = uniform((T)gp.gs);
+    const T gm1 = uniform((T)gp.pb);
+    const T prho = uniform((T)gp.pa);
+    const T tau = uniform((T)tau_d);
+    const T hx = uniform((T)gp.h[0]), hy = uniform((T)gp.h[1]), hz = uniform((T)gp.h[2]);
+    const T ihx = uniform((T)gp.inv_h[0]), ihy = uniform((T)gp.inv_h[1]), ihz = uniform((T)gp.inv_h[2]);
+    const T tohx = uniform((T)(tau_d * gp.inv_h[0])), tohy = uniform((T)(tau_d * gp.inv_h[1]));
+    const T tohz = uniform((T)(tau_d * gp.inv_h[2]));
     (void)hy; (void)ihy; (void)tohy; (void)hz; (void)ihz; (void)tohz; (void)tohx; (void)hx; (void)ihx; (void)tau;
-    const double thr = gp.vacuum_ratio * ctrl->rho_mean0;
+    const double thr = uniform(gp.vacuum_ratio * ctrl->rho_mean0);
 
     const int gx = x0 + tx, gy = y0 + ty;
     const bool valid = gx < nx && (NDIM < 2 || gy < ny);
@@ -721,7 +808,8 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
 #include "ppml_lagr_plane.inc"
         }
     }
-    publish_max(ctrl, sl ^ 1, (double)vmax, (double)cmax);
+    // no thread reads the velocity tile past the last plane's flux jobs
+    publish_max<NT>(ctrl, gp.mslots, sl ^ 1, slot_i, vmax, cmax, &s_vx[0][0]);
 }
 
 // Waves per SIMD the register allocator aims for in the Lagrangian kernel:
@@ -737,7 +825,8 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(lagr_wav
 {
     int bx, by, bz;
     block_tile(gp, bx, by, bz);
-    lagr_body<T, NDIM, TX, TY, G>(Wst, U, gp, ctrl, bx, by, bz, blockIdx.x == 0 && threadIdx.x == 0);
+    lagr_body<T, NDIM, TX, TY, G>(Wst, U, gp, ctrl, bx, by, bz, blockIdx.x == 0 && threadIdx.x == 0,
+                                  (int)(blockIdx.x % gp.mslots));
 }
 
 // ---------------------------------------------------------------------------
@@ -774,8 +863,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(euler_wa
     const int L = blockIdx.x - e->tile0;
     int bx, by, bz;
     tile_decode(e->gp, L, bx, by, bz);
-    euler_body<T, NDIM, TX, TY>((const T *)e->state, (T *)e->half, e->gp, e->ctrl, bx, by, bz,
-                                L == 0 && threadIdx.x == 0);
+    euler_body<T, NDIM, TX, TY>((const T *)e->state, (T *)e->half, e->gp, e->ctrl, bx, by, bz, L == 0);
 }
 
 template <typename T, int NDIM, int TX, int TY, int G>
@@ -786,7 +874,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(lagr_wav
     int bx, by, bz;
     tile_decode(e->gp, L, bx, by, bz);
     lagr_body<T, NDIM, TX, TY, G>((const T *)e->half, (T *)e->state, e->gp, e->ctrl, bx, by, bz,
-                                  L == 0 && threadIdx.x == 0);
+                                  L == 0 && threadIdx.x == 0, L % e->gp.mslots);
 }
 
 // Run parameters of every grid of a batch (steps[i] < 0: same as nsteps).
