@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstdarg>
@@ -17,6 +18,7 @@
 #include "../../include/ppml.h"
 #include "ppml_gravity.hpp"
 #include "ppml_kernels.hpp"
+#include "ppml_line.hpp"
 
 using namespace ppml;
 
@@ -285,6 +287,42 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
         k_lagr<T, NDIM, TL::tx, TL::ty, LG<T>::g><<<nbl, TL::nt, 0, g->stream>>>(W, Us, gl, g->ctrl);
         if (ev) (void)hipEventRecord(ev[3], g->stream);
     });
+}
+
+// 1-D grids whose steps run in one kernel on one CU (ppml_line.hpp).  Its time
+// follows the cells, that of the two stage launches is their dispatch; us per
+// step, line kernel against stage kernels: FP64 64 cells 1.9 / 10.0, 512 3.7 /
+// 11.7, 1024 5.4 / 12.2, 2048 9.8 / 12.4, 2500 12.4 / 12.5; FP32 64 1.4 / 8.1,
+// 512 2.3 / 9.4, 2048 5.8 / 10.3, 3500 9.5 / 10.6, 4096 11.3 / 10.7.
+template <typename T> constexpr long long line_cells() { return sizeof(T) == 8 ? 2304 : 3840; }
+
+bool line_grid(const ppml_desc *d)
+{
+    return d->ndim == 1 && d->n[0] <= (d->prec == PPML_FP64 ? line_cells<double>() : line_cells<float>());
+}
+
+// Threads of a line kernel's work groups for grids of up to n cells: a wave
+// per segment up to LINE_THREADS.
+int line_threads(long long n)
+{
+    return (int)std::min<long long>(LINE_THREADS, 64 * ((n + LINE_W - 1) / LINE_W));
+}
+
+// nsteps steps of a short 1-D grid; start: the run's parameters are these,
+// otherwise those of the control block.
+template <typename T> int launch_line(ppml_grid *g, long long nsteps, double dt_fixed, double t_stop, bool start)
+{
+    const long long n = g->gp.n[0];
+    const size_t lds = line_lds<T>(n);
+    if (lds > 65536)
+        HIPCHK(hipFuncSetAttribute((const void *)k_line<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    for (long long s = 0; s < nsteps; s += LINE_STEPS) {
+        const int m = (int)std::min<long long>(LINE_STEPS, nsteps - s);
+        k_line<T><<<1, line_threads(n), lds, g->stream>>>((T *)g->state, g->gp, g->ctrl, start && s == 0 ? nsteps : -1,
+                                                          dt_fixed, t_stop, m);
+    }
+    HIPCHK(hipGetLastError());
+    return PPML_OK;
 }
 
 // GEMMs of the sine transforms (column-major view of the C-order arrays:
@@ -935,12 +973,17 @@ int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop)
     if (!std::isfinite(dt_fixed) || !std::isfinite(t_stop)) return fail(PPML_EINVAL, "dt_fixed and t_stop must be finite");
     if (nsteps == 0) return PPML_OK;
     if (g->in_batch) return fail(PPML_ESTATE, "grid is stepped by its batch");
+    // per-step timing splits the step into its stage kernels
+    const bool timing = (size_t)(4 * (g->timed + 1)) <= g->ev.size();
+    const bool line = line_grid(&g->d);
+    if (line && !timing)
+        return g->d.prec == PPML_FP64 ? launch_line<double>(g, nsteps, dt_fixed, t_stop, true)
+                                      : launch_line<float>(g, nsteps, dt_fixed, t_stop, true);
     k_set_run<<<1, 1, 0, g->stream>>>(g->ctrl, dt_fixed, t_stop, (long long)nsteps);
     HIPCHK(hipGetLastError());  // before a capture attempt clears the last error
     // long calls replay the captured chunk (launch overhead once per
     // STEP_GRAPH steps); not while per-step timing is recorded, nor with
     // self-gravity (its library GEMMs stay outside captured graphs)
-    const bool timing = (size_t)(4 * (g->timed + 1)) <= g->ev.size();
     int s = 0;
     if (nsteps >= STEP_GRAPH && !timing && !g->gp.self_grav && step_graph(g)) {
         for (; s + STEP_GRAPH <= nsteps; s += STEP_GRAPH) HIPCHK(hipGraphLaunch(g->sexec, g->stream));
@@ -948,6 +991,9 @@ int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop)
     for (; s < nsteps; s++) {
         hipEvent_t *ev = nullptr;
         if ((size_t)(4 * (g->timed + 1)) <= g->ev.size()) ev = &g->ev[4 * g->timed];
+        if (line && !ev)  // past the timed steps
+            return g->d.prec == PPML_FP64 ? launch_line<double>(g, nsteps - s, 0.0, 0.0, false)
+                                          : launch_line<float>(g, nsteps - s, 0.0, 0.0, false);
         rc = g->d.prec == PPML_FP64 ? launch_step<double>(g, ev) : launch_step<float>(g, ev);
         if (rc) return rc;
         if (ev) g->timed++;
@@ -1019,7 +1065,11 @@ int ppml_step_noalloc(const ppml_desc *d, void *state_dev, double rho_mean0, dou
     // control block and the maxima slots by the reset, the mean density and the
     // partials by the kernels below, the stage output by the Eulerian kernel
     if ((rc = finish_set_async(&g, t0, rho_mean0))) return rc;
-    if (nsteps > 0) {
+    if (nsteps > 0 && line_grid(d)) {
+        rc = d->prec == PPML_FP64 ? launch_line<double>(&g, nsteps, dt_fixed, t_stop, true)
+                                  : launch_line<float>(&g, nsteps, dt_fixed, t_stop, true);
+        if (rc) return rc;
+    } else if (nsteps > 0) {
         k_set_run<<<1, 1, 0, g.stream>>>(g.ctrl, dt_fixed, t_stop, (long long)nsteps);
         HIPCHK(hipGetLastError());
         for (int s = 0; s < nsteps; s++) {
@@ -1263,7 +1313,9 @@ struct ppml_batch {
     BatchEntry *h_ents;   // pinned host copies
     int *h_steps;
     std::vector<int> entry_slot;
-    int goff[4], gn[4], gtiles[4];
+    int goff[4], gn[4], gtiles[4];  // grids stepped by the stage kernels, per dimensionality
+    int nline;            // short 1-D grids, first in the table: stepped by the line kernel
+    long long line_nmax;  // cells of the longest of them
     int tile[4];          // tile shape of the launches per dimensionality
     bool dirty;
     long long version;
@@ -1273,8 +1325,8 @@ struct ppml_batch {
     long long graph_version;
     // grids of different dimensionalities share nothing: their launch chains
     // run as parallel branches (streams forked from and joined to the batch
-    // stream, default priority), so the small 1-D launches overlap the 2-D
-    // and 3-D ones instead of adding their dispatch time
+    // stream, default priority), so the 1-D launches overlap the 2-D and 3-D
+    // ones instead of adding their time; side[0] runs the line kernel
     hipStream_t side[4];
     hipEvent_t ev_fork, ev_join[4];
 };
@@ -1287,18 +1339,30 @@ int batch_rebuild(ppml_batch *b)
 {
     int n = 0;
     b->entry_slot.clear();
-    for (int nd = 1; nd <= 3; nd++) {
-        b->goff[nd] = n;
-        int tiles = 0;
+    auto add = [&](int nd, bool line) {
         for (int s = 0; s < b->capacity; s++) {
             ppml_grid *g = b->slots[s];
-            if (!g || g->d.ndim != nd) continue;
+            if (!g || g->d.ndim != nd || line_grid(&g->d) != line) continue;
             BatchEntry &e = b->h_ents[n];
             e.gp = g->gp;
             set_tiling(e.gp, nd, b->tile[nd]);
+            e.state = g->state;
+            e.half = g->half;
+            e.ctrl = g->ctrl;
+            e.tile0 = 0;
+            e.pad = 0;
             b->entry_slot.push_back(s);
             n++;
         }
+    };
+    add(1, true);
+    b->nline = n;
+    b->line_nmax = 0;
+    for (int i = 0; i < n; i++) b->line_nmax = std::max<long long>(b->line_nmax, b->h_ents[i].gp.n[0]);
+    for (int nd = 1; nd <= 3; nd++) {
+        b->goff[nd] = n;
+        int tiles = 0;
+        add(nd, false);
         b->gn[nd] = n - b->goff[nd];
         if (nd == 3 && b->gn[3] > 0) {
             // one chunk length for all 3-D grids, fitted to the Lagrangian
@@ -1314,12 +1378,7 @@ int batch_rebuild(ppml_batch *b)
         }
         for (int i = b->goff[nd]; i < n; i++) {
             BatchEntry &e = b->h_ents[i];
-            const ppml_grid *g = b->slots[b->entry_slot[i]];
-            e.state = g->state;
-            e.half = g->half;
-            e.ctrl = g->ctrl;
             e.tile0 = tiles;
-            e.pad = 0;
             tiles += e.gp.tiles[0] * e.gp.tiles[1] * e.gp.tiles[2];
         }
         b->gtiles[nd] = tiles;
@@ -1354,20 +1413,35 @@ template <typename T, int NDIM> void batch_chain(ppml_batch *b, int nsteps, hipS
     }
 }
 
+// nsteps steps of the short 1-D grids.
+template <typename T> int batch_lines(ppml_batch *b, int nsteps, hipStream_t st)
+{
+    const size_t lds = line_lds<T>(b->line_nmax);
+    if (lds > 65536)
+        HIPCHK(hipFuncSetAttribute((const void *)k_line_batch<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    for (int s = 0; s < nsteps; s += LINE_STEPS)
+        k_line_batch<T><<<b->nline, line_threads(b->line_nmax), lds, st>>>(b->d_ents,
+                                                                          std::min(LINE_STEPS, nsteps - s));
+    return PPML_OK;
+}
+
 // nsteps steps of every grid: one chain of stage launches per dimensionality
-// present; with more than one, each chain runs on a side stream forked from
-// the batch stream and joined back to it.
+// present, and the line kernel; with more than one, each runs on a side stream
+// forked from the batch stream and joined back to it.
 template <typename T> int batch_enqueue(ppml_batch *b, int nsteps)
 {
-    int present = 0;
+    int present = b->nline ? 1 : 0;
     for (int nd = 1; nd <= 3; nd++) present += b->gn[nd] ? 1 : 0;
     const bool fork = present > 1;
     if (fork) HIPCHK(hipEventRecord(b->ev_fork, b->stream));
-    for (int nd = 1; nd <= 3; nd++) {
-        if (!b->gn[nd]) continue;
+    for (int nd = 0; nd <= 3; nd++) {
+        if (!(nd == 0 ? b->nline : b->gn[nd])) continue;
         hipStream_t st = fork ? b->side[nd] : b->stream;
         if (fork) HIPCHK(hipStreamWaitEvent(st, b->ev_fork, 0));
-        if (nd == 1) batch_chain<T, 1>(b, nsteps, st);
+        if (nd == 0) {
+            const int rc = batch_lines<T>(b, nsteps, st);
+            if (rc) return rc;
+        } else if (nd == 1) batch_chain<T, 1>(b, nsteps, st);
         else if (nd == 2) batch_chain<T, 2>(b, nsteps, st);
         else batch_chain<T, 3>(b, nsteps, st);
         HIPCHK(hipGetLastError());
@@ -1412,6 +1486,8 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
     b->h_ents = nullptr;
     b->h_steps = nullptr;
     b->dirty = true;
+    b->nline = 0;
+    b->line_nmax = 0;
     for (int nd = 0; nd < 4; nd++) b->tile[nd] = 0;
     b->version = 0;
     b->graph = nullptr;
@@ -1426,7 +1502,7 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
     hipError_t e = hipMalloc(&b->d_ents, (size_t)capacity * sizeof(BatchEntry));
     if (e == hipSuccess) e = hipMalloc(&b->d_steps, (size_t)capacity * sizeof(int));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
-    for (int nd = 1; nd <= 3 && e == hipSuccess; nd++) {
+    for (int nd = 0; nd <= 3 && e == hipSuccess; nd++) {
         e = hipStreamCreateWithFlags(&b->side[nd], hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join[nd], hipEventDisableTiming);
     }
@@ -1437,7 +1513,7 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
         if (b->d_steps) (void)hipFree(b->d_steps);
         if (b->h_ents) (void)hipHostFree(b->h_ents);
         if (b->h_steps) (void)hipHostFree(b->h_steps);
-        for (int nd = 1; nd <= 3; nd++) {
+        for (int nd = 0; nd <= 3; nd++) {
             if (b->side[nd]) (void)hipStreamDestroy(b->side[nd]);
             if (b->ev_join[nd]) (void)hipEventDestroy(b->ev_join[nd]);
         }
@@ -1592,7 +1668,7 @@ int ppml_batch_destroy(ppml_batch *b)
     (void)hipFree(b->d_steps);
     (void)hipHostFree(b->h_ents);
     (void)hipHostFree(b->h_steps);
-    for (int nd = 1; nd <= 3; nd++) {
+    for (int nd = 0; nd <= 3; nd++) {
         (void)hipStreamDestroy(b->side[nd]);
         (void)hipEventDestroy(b->ev_join[nd]);
     }

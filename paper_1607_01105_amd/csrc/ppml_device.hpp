@@ -119,6 +119,8 @@ __device__ __forceinline__ double med0(double a, double b)
     return __builtin_fmax(__builtin_fmin(a, b), __builtin_fmin(__builtin_fmax(a, b), 0.0));
 }
 __device__ __forceinline__ double dmin(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ float dmax(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ double dmax(double a, double b) { return __builtin_fmax(a, b); }
 
 // A value that is the same in every lane, held in scalar registers.  Results
 // of floating-point conversions and arithmetic land in vector registers even

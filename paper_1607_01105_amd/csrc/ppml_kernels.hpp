@@ -17,6 +17,8 @@
 // per-thread register pipeline over the thread's own column (loads run three
 // planes ahead), so no z halo is ever staged.  2-D and 1-D grids use the same
 // kernels with one plane (and TY = 1 in 1-D).
+#pragma once
+
 #include "ppml_device.hpp"
 
 namespace ppml {
