@@ -140,7 +140,9 @@ typedef struct {
  * ppml_tile_shape gives the x and y extent of shape `variant` (a work group
  * of tx*ty threads owns a tx x ty column of cells; 3-D kernels march it
  * along z).  Used by the autotuner, which times the shapes on the caller's
- * workload; every shape computes bit-identical results. */
+ * workload; every shape computes bit-identical results.  The kernels of 2-D
+ * grids and of short 1-D grids (up to 2304 cells in FP64, 3840 in FP32) have
+ * no tiles: the shape changes nothing there. */
 int ppml_tile_count(int32_t ndim);
 int ppml_tile_shape(int32_t ndim, int32_t variant, int32_t *tx, int32_t *ty);
 
@@ -184,7 +186,9 @@ int ppml_set_conserved(ppml_grid *g, const double *const *f, double rho_mean0, d
  * itself are reported by the next synchronizing call.  Calls of 32 steps or
  * more replay a HIP graph of 32 steps (captured once per grid on a private
  * stream, launched on the grid's stream) unless per-step timing is on or
- * the grid has self-gravity; the results are the same bits.
+ * the grid has self-gravity; short 1-D grids take all steps of a call (1024 at
+ * a time) in one kernel unless per-step timing is on; the results are the
+ * same bits.
  * Errors: PPML_EINVAL (nsteps < 0), PPML_ESTATE (state never set), PPML_EHIP. */
 int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop);
 
@@ -248,7 +252,8 @@ int ppml_get_timing_split(ppml_grid *g, double ms[3], int64_t *nsteps);
 
 /* ---- Batches: many independent grids stepped together ------------------
  * A batch steps all its grids in the same kernel launches (one Eulerian and
- * one Lagrangian launch per step and dimensionality present; the launch
+ * one Lagrangian launch per step and dimensionality present, and one launch
+ * of all the steps of the short 1-D grids; the launch
  * chains of different dimensionalities run concurrently on streams the
  * batch forks from its stream and joins back), optionally recorded once into
  * a HIP graph and replayed.  Each grid keeps its own

@@ -36,8 +36,11 @@ def _command(out: str, exact: bool) -> list[str]:
         # subnormals flushed to zero, which drops the operand scaling around
         # v_rcp_f32 / v_sqrt_f32 (no state value of a physical run comes near
         # 1e-38); FP64 keeps correctly rounded division, square root and
-        # subnormals
-        flags += ["-fno-hip-fp32-correctly-rounded-divide-sqrt", "-fgpu-flush-denormals-to-zero"]
+        # subnormals.  Multiply-adds are contracted within an expression, not
+        # across statements: which operations fuse then follows from the source
+        # alone, and every kernel that inlines a formula gives the same bits
+        # (solo and batched launches, tile shapes, rows per wave)
+        flags += ["-fno-hip-fp32-correctly-rounded-divide-sqrt", "-fgpu-flush-denormals-to-zero", "-ffp-contract=on"]
     # rocBLAS runs the GEMMs of the self-gravity sine transforms
     return [HIPCC, *flags, SRC, "-o", out + ".tmp", "-L/opt/rocm/lib", "-lrocblas", "-Wl,-rpath,/opt/rocm/lib"]
 

@@ -19,6 +19,7 @@
 #include "ppml_gravity.hpp"
 #include "ppml_kernels.hpp"
 #include "ppml_line.hpp"
+#include "ppml_sheet.hpp"
 
 using namespace ppml;
 
@@ -69,6 +70,21 @@ template <int NDIM, typename F> void with_tile(int v, F &&f)
         default: f(Tile<32, 8>{}); break;
         }
     }
+}
+
+// Rows per wave the 2-D kernels are compiled for; FP64 spills past two.
+constexpr int SHEET_ROWS[] = {1, 2, 3, 4, 8};
+template <typename T, typename F> void with_rows(int r, F &&f)
+{
+    if constexpr (sizeof(T) == 4) {
+        switch (r) {
+        case 8: return f(std::integral_constant<int, 8>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 3: return f(std::integral_constant<int, 3>{});
+        }
+    }
+    if (r == 2) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, 1>{});
 }
 
 // Fields per LDS pass of the Lagrangian kernel (all six in FP32; FP64 in
@@ -250,6 +266,15 @@ struct ppml_grid {
 
 namespace {
 
+// Work groups of a stage launch for one grid: one per tile, in 2-D one per four
+// strips (a wave each).
+int work_groups(const GridParams &gp)
+{
+    constexpr int per = SHEET_THREADS / 64;
+    const int t = gp.tiles[0] * gp.tiles[1] * gp.tiles[2];
+    return gp.ndim == 2 ? (t + per - 1) / per : t;
+}
+
 template <typename T> void launch_speeds(ppml_grid *g)
 {
     const T *U = (const T *)g->state;
@@ -266,27 +291,38 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
     const T *U = (const T *)g->state;
     T *Us = (T *)g->state;
     T *W = (T *)g->half;
-    with_tile<NDIM>(g->d.tile, [&](auto tl) {
-        using TL = decltype(tl);
-        const GridParams &ge = g->gpE;
-        const GridParams &gl = g->gpL;
-        const int nbe = ge.tiles[0] * ge.tiles[1] * ge.tiles[2];
-        const int nbl = gl.tiles[0] * gl.tiles[1] * gl.tiles[2];
+    if constexpr (NDIM == 2) {
         if (ev) (void)hipEventRecord(ev[1], g->stream);
-        if constexpr (NDIM == 3) {
-            if (ge.potential == POT_HALO)
-                k_euler<T, 3, TL::tx, TL::ty, 2><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
-            else if (ge.self_grav)
-                k_euler<T, 3, TL::tx, TL::ty, 1><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
-            else
-                k_euler<T, 3, TL::tx, TL::ty><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
-        } else {
-            k_euler<T, NDIM, TL::tx, TL::ty><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
-        }
-        if (ev) (void)hipEventRecord(ev[2], g->stream);
-        k_lagr<T, NDIM, TL::tx, TL::ty, LG<T>::g><<<nbl, TL::nt, 0, g->stream>>>(W, Us, gl, g->ctrl);
+        with_rows<T>(g->gp.cz, [&](auto rows) {
+            constexpr int R = decltype(rows)::value;
+            k_euler_sheet<T, R><<<work_groups(g->gp), SHEET_THREADS, 0, g->stream>>>(U, W, g->gp, g->ctrl);
+            if (ev) (void)hipEventRecord(ev[2], g->stream);
+            k_lagr_sheet<T, R><<<work_groups(g->gp), SHEET_THREADS, 0, g->stream>>>(W, Us, g->gp, g->ctrl);
+        });
         if (ev) (void)hipEventRecord(ev[3], g->stream);
-    });
+    } else {
+        with_tile<NDIM>(g->d.tile, [&](auto tl) {
+            using TL = decltype(tl);
+            const GridParams &ge = g->gpE;
+            const GridParams &gl = g->gpL;
+            const int nbe = work_groups(ge);
+            const int nbl = work_groups(gl);
+            if (ev) (void)hipEventRecord(ev[1], g->stream);
+            if constexpr (NDIM == 3) {
+                if (ge.potential == POT_HALO)
+                    k_euler<T, 3, TL::tx, TL::ty, 2><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
+                else if (ge.self_grav)
+                    k_euler<T, 3, TL::tx, TL::ty, 1><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
+                else
+                    k_euler<T, 3, TL::tx, TL::ty><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
+            } else {
+                k_euler<T, NDIM, TL::tx, TL::ty><<<nbe, TL::nt, 0, g->stream>>>(U, W, ge, g->ctrl);
+            }
+            if (ev) (void)hipEventRecord(ev[2], g->stream);
+            k_lagr<T, NDIM, TL::tx, TL::ty, LG<T>::g><<<nbl, TL::nt, 0, g->stream>>>(W, Us, gl, g->ctrl);
+            if (ev) (void)hipEventRecord(ev[3], g->stream);
+        });
+    }
 }
 
 // 1-D grids whose steps run in one kernel on one CU (ppml_line.hpp).  Its time
@@ -300,6 +336,13 @@ bool line_grid(const ppml_desc *d)
 {
     return d->ndim == 1 && d->n[0] <= (d->prec == PPML_FP64 ? line_cells<double>() : line_cells<float>());
 }
+
+// Beside the launches of 2-D or 3-D grids the line kernel also takes longer
+// 1-D grids, in memory instead of LDS: a second chain of launches slows the
+// first (24 1-D and 24 2-D grids FP32, one of 3.9 k cells: 37 us per step with
+// both chains, 28 with one).  Past a few thousand cells its time per step would
+// pass that of a 2-D chain.
+constexpr long long LINE_BATCH_CELLS = 4608;
 
 // Threads of a line kernel's work groups for grids of up to n cells: a wave
 // per segment up to LINE_THREADS.
@@ -562,11 +605,48 @@ template <typename T> void stage_slots(int device, int tile, int xf, long long &
     slots_l = (long long)cus * (bl > 0 ? bl : 2);
 }
 
+// Rows per wave of the 2-D grids that share a launch.  A row more costs a wave
+// about what its first costs beyond the rows shared (1 + r, in rows); the 1024
+// SIMDs work off the waves in turn, a wave alone on its SIMD taking 1.3 of its
+// share.  us per step at 1, 2, 3, 8 rows, FP32: 256^2 11.9, 11.4, 12.7, 19.1;
+// 371^2 15.4, 15.6, 14.3, 20.9; 768x700 32.3, 27.2, 28.6, 31.8; 1500^2 97, 78,
+// 68, 65 (the tile kernels before: 13.9, 17.0, 31.2, 93); FP64 at 1, 2 rows:
+// 256^2 16.6, 15.3; 1500^2 189, 147 (18.7, 216).
+int sheet_rows(const std::vector<const GridParams *> &gps, int prec)
+{
+    int best = 1;
+    double best_t = 1e300;
+    for (int r : SHEET_ROWS) {
+        if (prec == PPML_FP64 && r > 2) break;
+        double waves = 0.0;
+        for (const GridParams *gp : gps)
+            waves += (double)((gp->n[0] + SHEET_W - 1) / SHEET_W) * ((gp->n[1] + r - 1) / r);
+        const double t = (1.0 + r) * std::max(std::ceil(waves / 1024.0), 1.3);
+        if (t < best_t) {
+            best_t = t;
+            best = r;
+        }
+    }
+    return best;
+}
+
+void set_rows(GridParams &gp, int rows)
+{
+    gp.tiles[0] = (gp.n[0] + SHEET_W - 1) / SHEET_W;
+    gp.tiles[1] = (gp.n[1] + rows - 1) / rows;
+    gp.tiles[2] = 1;
+    gp.cz = rows;
+}
+
 // Work-group tiling of a grid for tile shape v: x/y tiles, and a z chunk
 // small enough that a 3-D grid alone gives the launch a few thousand work
 // groups (batches then fit the chunks of their 3-D grids together).
-void set_tiling(GridParams &gp, int ndim, int v)
+void set_tiling(GridParams &gp, int ndim, int prec, int v)
 {
+    if (ndim == 2) {
+        set_rows(gp, sheet_rows({&gp}, prec));
+        return;
+    }
     const int tx = TILE_X[ndim][v], ty = TILE_Y[ndim][v];
     gp.tiles[0] = (gp.n[0] + tx - 1) / tx;
     gp.tiles[1] = ndim >= 2 ? (gp.n[1] + ty - 1) / ty : 1;
@@ -685,7 +765,7 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
     gp.potential = d->potential;
     gp.first_order = (d->flags & PPML_FLAG_FIRST_ORDER) ? 1 : 0;
     for (int i = 0; i < 8; i++) gp.pot[i] = d->pot[i];
-    set_tiling(gp, d->ndim, d->tile);
+    set_tiling(gp, d->ndim, d->prec, d->tile);
     // conserved ghost states of inflow faces, converted in FP64 as the state
     // is, into the control block
     double tab[6][6];
@@ -1309,13 +1389,15 @@ struct ppml_batch {
     int prec;        // precision shared by all admitted grids (-1: none yet)
     std::vector<ppml_grid *> slots;
     BatchEntry *d_ents;   // device table, grouped by dimensionality
-    int *d_steps;         // device per-entry step counts
+    int *d_steps;         // device per-entry step counts, then ...
+    int *d_first;         // ... first work group of every entry in its launch
     BatchEntry *h_ents;   // pinned host copies
     int *h_steps;
     std::vector<int> entry_slot;
     int goff[4], gn[4], gtiles[4];  // grids stepped by the stage kernels, per dimensionality
-    int nline;            // short 1-D grids, first in the table: stepped by the line kernel
-    long long line_nmax;  // cells of the longest of them
+    int rows2;            // rows per wave of the 2-D launches
+    int nline, nlds;      // 1-D grids stepped by the line kernel, first in the table; those of them in LDS
+    long long line_nmax, lds_nmax;  // cells of the longest
     int tile[4];          // tile shape of the launches per dimensionality
     bool dirty;
     long long version;
@@ -1339,13 +1421,19 @@ int batch_rebuild(ppml_batch *b)
 {
     int n = 0;
     b->entry_slot.clear();
-    auto add = [&](int nd, bool line) {
+    bool beside = false;  // grids of more than one dimension share the batch
+    for (const ppml_grid *g : b->slots) beside = beside || (g && g->d.ndim > 1);
+    // kind: 0 stage kernels, 1 line kernel in LDS, 2 line kernel in memory
+    auto kind_of = [&](const ppml_grid *g) {
+        return line_grid(&g->d) ? 1 : (beside && g->d.ndim == 1 && g->d.n[0] <= LINE_BATCH_CELLS ? 2 : 0);
+    };
+    auto add = [&](int nd, int kind) {
         for (int s = 0; s < b->capacity; s++) {
             ppml_grid *g = b->slots[s];
-            if (!g || g->d.ndim != nd || line_grid(&g->d) != line) continue;
+            if (!g || g->d.ndim != nd || kind_of(g) != kind) continue;
             BatchEntry &e = b->h_ents[n];
             e.gp = g->gp;
-            set_tiling(e.gp, nd, b->tile[nd]);
+            set_tiling(e.gp, nd, b->prec, b->tile[nd]);
             e.state = g->state;
             e.half = g->half;
             e.ctrl = g->ctrl;
@@ -1355,15 +1443,25 @@ int batch_rebuild(ppml_batch *b)
             n++;
         }
     };
-    add(1, true);
+    add(1, 1);
+    b->nlds = n;
+    b->lds_nmax = 0;
+    for (int i = 0; i < n; i++) b->lds_nmax = std::max<long long>(b->lds_nmax, b->h_ents[i].gp.n[0]);
+    add(1, 2);
     b->nline = n;
     b->line_nmax = 0;
     for (int i = 0; i < n; i++) b->line_nmax = std::max<long long>(b->line_nmax, b->h_ents[i].gp.n[0]);
     for (int nd = 1; nd <= 3; nd++) {
         b->goff[nd] = n;
         int tiles = 0;
-        add(nd, false);
+        add(nd, 0);
         b->gn[nd] = n - b->goff[nd];
+        if (nd == 2 && b->gn[2] > 0) {
+            std::vector<const GridParams *> gps;
+            for (int i = b->goff[2]; i < n; i++) gps.push_back(&b->h_ents[i].gp);
+            b->rows2 = sheet_rows(gps, b->prec);
+            for (int i = b->goff[2]; i < n; i++) set_rows(b->h_ents[i].gp, b->rows2);
+        }
         if (nd == 3 && b->gn[3] > 0) {
             // one chunk length for all 3-D grids, fitted to the Lagrangian
             // kernel's resident work groups (its start-up: 6 z-only planes,
@@ -1379,12 +1477,16 @@ int batch_rebuild(ppml_batch *b)
         for (int i = b->goff[nd]; i < n; i++) {
             BatchEntry &e = b->h_ents[i];
             e.tile0 = tiles;
-            tiles += e.gp.tiles[0] * e.gp.tiles[1] * e.gp.tiles[2];
+            tiles += work_groups(e.gp);
         }
         b->gtiles[nd] = tiles;
     }
     if (n > 0) {
         HIPCHK(hipMemcpyAsync(b->d_ents, b->h_ents, (size_t)n * sizeof(BatchEntry), hipMemcpyHostToDevice, b->stream));
+        int *first = b->h_steps + b->capacity;
+        for (int i = 0; i < n; i++) first[i] = b->h_ents[i].tile0;
+        b->d_first = b->d_steps + b->capacity;
+        HIPCHK(hipMemcpyAsync(b->d_first, first, (size_t)n * sizeof(int), hipMemcpyHostToDevice, b->stream));
         HIPCHK(hipStreamSynchronize(b->stream));
     }
     b->dirty = false;
@@ -1395,14 +1497,25 @@ int batch_rebuild(ppml_batch *b)
 template <typename T, int NDIM> void batch_stage(ppml_batch *b, bool lagr, hipStream_t st)
 {
     if (!b->gn[NDIM]) return;
-    with_tile<NDIM>(b->tile[NDIM], [&](auto tl) {
-        using TL = decltype(tl);
-        const BatchEntry *e = b->d_ents + b->goff[NDIM];
-        if (lagr)
-            k_lagr_batch<T, NDIM, TL::tx, TL::ty, LG<T>::g><<<b->gtiles[NDIM], TL::nt, 0, st>>>(e, b->gn[NDIM]);
-        else
-            k_euler_batch<T, NDIM, TL::tx, TL::ty><<<b->gtiles[NDIM], TL::nt, 0, st>>>(e, b->gn[NDIM]);
-    });
+    if constexpr (NDIM == 2) {
+        const BatchEntry *e = b->d_ents + b->goff[2];
+        const int *first = b->d_first + b->goff[2];
+        with_rows<T>(b->rows2, [&](auto rows) {
+            constexpr int R = decltype(rows)::value;
+            if (lagr) k_lagr_sheet_batch<T, R><<<b->gtiles[2], SHEET_THREADS, 0, st>>>(e, first, b->gn[2]);
+            else k_euler_sheet_batch<T, R><<<b->gtiles[2], SHEET_THREADS, 0, st>>>(e, first, b->gn[2]);
+        });
+    } else {
+        with_tile<NDIM>(b->tile[NDIM], [&](auto tl) {
+            using TL = decltype(tl);
+            const BatchEntry *e = b->d_ents + b->goff[NDIM];
+            const int *first = b->d_first + b->goff[NDIM];
+            if (lagr)
+                k_lagr_batch<T, NDIM, TL::tx, TL::ty, LG<T>::g><<<b->gtiles[NDIM], TL::nt, 0, st>>>(e, first, b->gn[NDIM]);
+            else
+                k_euler_batch<T, NDIM, TL::tx, TL::ty><<<b->gtiles[NDIM], TL::nt, 0, st>>>(e, first, b->gn[NDIM]);
+        });
+    }
 }
 
 template <typename T, int NDIM> void batch_chain(ppml_batch *b, int nsteps, hipStream_t st)
@@ -1416,12 +1529,12 @@ template <typename T, int NDIM> void batch_chain(ppml_batch *b, int nsteps, hipS
 // nsteps steps of the short 1-D grids.
 template <typename T> int batch_lines(ppml_batch *b, int nsteps, hipStream_t st)
 {
-    const size_t lds = line_lds<T>(b->line_nmax);
+    const size_t lds = line_lds<T>(b->lds_nmax);
     if (lds > 65536)
         HIPCHK(hipFuncSetAttribute((const void *)k_line_batch<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     for (int s = 0; s < nsteps; s += LINE_STEPS)
-        k_line_batch<T><<<b->nline, line_threads(b->line_nmax), lds, st>>>(b->d_ents,
-                                                                          std::min(LINE_STEPS, nsteps - s));
+        k_line_batch<T><<<b->nline, line_threads(b->line_nmax), lds, st>>>(
+            b->d_ents, b->nlds, std::min(LINE_STEPS, nsteps - s));
     return PPML_OK;
 }
 
@@ -1486,8 +1599,10 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
     b->h_ents = nullptr;
     b->h_steps = nullptr;
     b->dirty = true;
-    b->nline = 0;
-    b->line_nmax = 0;
+    b->nline = b->nlds = 0;
+    b->line_nmax = b->lds_nmax = 0;
+    b->rows2 = 1;
+    b->d_first = nullptr;
     for (int nd = 0; nd < 4; nd++) b->tile[nd] = 0;
     b->version = 0;
     b->graph = nullptr;
@@ -1500,14 +1615,14 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
     }
     b->ev_fork = nullptr;
     hipError_t e = hipMalloc(&b->d_ents, (size_t)capacity * sizeof(BatchEntry));
-    if (e == hipSuccess) e = hipMalloc(&b->d_steps, (size_t)capacity * sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&b->d_steps, (size_t)2 * capacity * sizeof(int));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
     for (int nd = 0; nd <= 3 && e == hipSuccess; nd++) {
         e = hipStreamCreateWithFlags(&b->side[nd], hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join[nd], hipEventDisableTiming);
     }
     if (e == hipSuccess) e = hipHostMalloc(&b->h_ents, (size_t)capacity * sizeof(BatchEntry), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_steps, (size_t)capacity * sizeof(int), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&b->h_steps, (size_t)2 * capacity * sizeof(int), hipHostMallocDefault);
     if (e != hipSuccess) {
         if (b->d_ents) (void)hipFree(b->d_ents);
         if (b->d_steps) (void)hipFree(b->d_steps);

@@ -15,8 +15,9 @@
 // and marches along z over a chunk of planes.  The x and y directions of each
 // plane are computed from LDS tiles with a 3-cell halo; the z direction is a
 // per-thread register pipeline over the thread's own column (loads run three
-// planes ahead), so no z halo is ever staged.  2-D and 1-D grids use the same
-// kernels with one plane (and TY = 1 in 1-D).
+// planes ahead), so no z halo is ever staged.  Long 1-D grids use the same
+// kernels with one plane and TY = 1; short 1-D grids and 2-D grids have kernels
+// of their own (ppml_line.hpp, ppml_sheet.hpp).
 #pragma once
 
 #include "ppml_device.hpp"
@@ -378,13 +379,13 @@ __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restric
     constexpr size_t GROUPS3 = NT >= 64 ? (size_t)12 / (NT / 64) : 12;  // groups per CU for 3 waves/SIMD
     constexpr size_t B_SEP = (B_TILE + B_IFACE + B_REST + 2047) & ~(size_t)2047;
     constexpr size_t B_OVL = ((B_TILE > B_IFACE ? B_TILE : B_IFACE) + B_REST + 2047) & ~(size_t)2047;
-    // 1-D and 2-D kernels hold few registers, so LDS alone decides how many
-    // groups fit (up to 32 waves per CU): overlay where that adds a group
+    // 1-D kernels hold few registers, so LDS alone decides how many groups fit
+    // (up to 32 waves per CU): overlay where that adds a group
     constexpr size_t GMAX = NT >= 64 ? (size_t)32 / (NT / 64) : 32;
     constexpr size_t G_SEP = 163840 / B_SEP < GMAX ? 163840 / B_SEP : GMAX;
     constexpr size_t G_OVL = 163840 / B_OVL < GMAX ? 163840 / B_OVL : GMAX;
     constexpr bool OVERLAY = (sizeof(T) == 8 && GROUPS3 * B_OVL <= 163840 && GROUPS3 * B_SEP > 163840) ||
-                             (NDIM <= 2 && G_OVL > G_SEP);
+                             (NDIM == 1 && G_OVL > G_SEP);
     constexpr size_t B_UNION = OVERLAY ? (B_TILE > B_IFACE ? B_TILE : B_IFACE) : B_TILE + B_IFACE;
     __shared__ __align__(16) unsigned char s_union[B_UNION];
     T *const s_vx = reinterpret_cast<T *>(s_union);
@@ -605,7 +606,7 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
     constexpr bool PIPE = sizeof(T) == 4 && NDIM == 3 && G >= NF;
     constexpr int NBUF = PIPE ? 2 : 1;
     // field slots of the tiles: G per pass, or all NF fields when they are
-    // fewer (1-D and 2-D FP32), so that no slot of LDS goes unused
+    // fewer (1-D FP32), so that no slot of LDS goes unused
     constexpr int GL = G < NF ? G : NF;
     __shared__ T s_f[NBUF][GL][PS];
     __shared__ T s_qx[GL][NXQ];
@@ -846,22 +847,30 @@ struct BatchEntry {
     int pad;
 };
 
-__device__ __forceinline__ int batch_entry(const BatchEntry *__restrict__ ents, int ne, int b)
+// Grid of work group b: the last entry whose first work group is not past b.
+// Every lane of a wave looks at one of 64 entries spread over the range that is
+// left, so that a table of 64 grids takes one memory latency and one of 4096 two, where
+// a binary search takes one per bit.
+__device__ __forceinline__ int batch_entry(const int *__restrict__ first, int ne, int b)
 {
-    int lo = 0, hi = ne - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (ents[mid].tile0 <= b) lo = mid;
-        else hi = mid - 1;
+    const int ln = threadIdx.x & 63;
+    int lo = 0, span = ne;
+    while (span > 1) {
+        const int st = (span + 63) >> 6;  // entries per lane
+        const int i = lo + ln * st;
+        const bool in = ln * st < span && first[i] <= b;
+        const int k = __builtin_popcountll(__ballot(in)) - 1;  // (the first of the range is never past b)
+        lo += k * st;
+        span = span - k * st < st ? span - k * st : st;
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 template <typename T, int NDIM, int TX, int TY>
 __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(euler_waves<T, NDIM, 0>()))) void k_euler_batch(
-    const BatchEntry *__restrict__ ents, int ne)
+    const BatchEntry *__restrict__ ents, const int *__restrict__ first, int ne)
 {
-    const BatchEntry *e = ents + batch_entry(ents, ne, blockIdx.x);
+    const BatchEntry *e = ents + batch_entry(first, ne, blockIdx.x);
     const int L = blockIdx.x - e->tile0;
     int bx, by, bz;
     tile_decode(e->gp, L, bx, by, bz);
@@ -869,9 +878,10 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(euler_wa
 }
 
 template <typename T, int NDIM, int TX, int TY, int G>
-__global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(lagr_waves<T, NDIM>()))) void k_lagr_batch(const BatchEntry *__restrict__ ents, int ne)
+__global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(lagr_waves<T, NDIM>()))) void k_lagr_batch(
+    const BatchEntry *__restrict__ ents, const int *__restrict__ first, int ne)
 {
-    const BatchEntry *e = ents + batch_entry(ents, ne, blockIdx.x);
+    const BatchEntry *e = ents + batch_entry(first, ne, blockIdx.x);
     const int L = blockIdx.x - e->tile0;
     int bx, by, bz;
     tile_decode(e->gp, L, bx, by, bz);

@@ -115,16 +115,18 @@ __device__ __forceinline__ double read_lane(double v, int l)
 
 // Up to nlaunch steps of one grid by the whole work group (LINE_THREADS
 // threads at most).  run_steps >= 0 starts a run of that many steps with the
-// given parameters; otherwise the control block holds the run.
-template <typename T>
-__device__ __forceinline__ void line_body(T *__restrict__ U, const GridParams &gp, Ctrl *ctrl, long long run_steps,
+// given parameters; otherwise the control block holds the run.  LDS: the two
+// buffers lie in LDS; otherwise they are the state U and the stage output W in
+// memory (for grids that LDS does not hold).
+template <typename T, bool LDS>
+__device__ __forceinline__ void line_body(T *U, T *W, const GridParams &gp, Ctrl *ctrl, long long run_steps,
                                           double run_dt, double run_t_stop, int nlaunch, T *lds)
 {
     constexpr int NF = 4;
     const int n = gp.n[0];
     const int nseg = (n + LINE_W - 1) / LINE_W;
     const int wv = wave_id(), ln = threadIdx.x & 63, nw = (int)blockDim.x >> 6;
-    T *const red = lds + 2 * NF * n;  // [2 parities][|v|, c][waves]
+    T *const red = lds + (LDS ? 2 * NF * n : 0);  // [2 parities][|v|, c][waves]
 
     const int set = ctrl->slot_cur;
     long long steps_left = run_steps >= 0 ? run_steps : ctrl->steps_left;
@@ -146,7 +148,8 @@ __device__ __forceinline__ void line_body(T *__restrict__ U, const GridParams &g
     (void)hx;
     (void)ihx;
 
-    for (int i = threadIdx.x; i < NF * n; i += blockDim.x) lds[i] = U[i];
+    if constexpr (LDS)
+        for (int i = threadIdx.x; i < NF * n; i += blockDim.x) lds[i] = U[i];
     __syncthreads();
 
     // source cell, momentum flip and inflow face of the lane's cell in a
@@ -173,8 +176,15 @@ __device__ __forceinline__ void line_body(T *__restrict__ U, const GridParams &g
         const T tau = uniform((T)tau_d);
         const T tohx = uniform((T)(tau_d * gp.inv_h[0]));
         (void)tohx;
-        const T *src = lds + (taken & 1) * NF * n;
-        T *dst = lds + ((taken & 1) ^ 1) * NF * n;
+        const T *src;
+        T *dst;
+        if constexpr (LDS) {
+            src = lds + (taken & 1) * NF * n;
+            dst = lds + ((taken & 1) ^ 1) * NF * n;
+        } else {
+            src = taken & 1 ? W : U;
+            dst = taken & 1 ? U : W;
+        }
         T vmax = T(0), cmax = T(0);
 #pragma unroll 1
         for (int seg = wv; seg < nseg; seg += nw) {
@@ -306,8 +316,8 @@ __device__ __forceinline__ void line_body(T *__restrict__ U, const GridParams &g
         cm = (double)read_lane(m, 31);
     }
 
-    if (taken > 0) {
-        const T *fin = lds + (taken & 1) * NF * n;
+    if (LDS ? taken > 0 : taken & 1) {
+        const T *fin = LDS ? lds + (taken & 1) * NF * n : W;
         for (int i = threadIdx.x; i < NF * n; i += blockDim.x) U[i] = fin[i];
     }
     if (__any(bad) && ln == 0) atomicOr(&ctrl->err, 1);
@@ -333,18 +343,23 @@ __device__ __forceinline__ void line_body(T *__restrict__ U, const GridParams &g
 extern __shared__ __align__(16) unsigned char line_shared[];
 
 template <typename T>
-__global__ __launch_bounds__(LINE_THREADS) void k_line(T *__restrict__ U, GridParams gp, Ctrl *ctrl, long long run_steps,
+__global__ __launch_bounds__(LINE_THREADS) void k_line(T *U, GridParams gp, Ctrl *ctrl, long long run_steps,
                                                        double run_dt, double run_t_stop, int nlaunch)
 {
-    line_body<T>(U, gp, ctrl, run_steps, run_dt, run_t_stop, nlaunch, reinterpret_cast<T *>(line_shared));
+    line_body<T, true>(U, nullptr, gp, ctrl, run_steps, run_dt, run_t_stop, nlaunch, reinterpret_cast<T *>(line_shared));
 }
 
-// The short 1-D grids of a batch, one work group each.
+// The short 1-D grids of a batch, one work group each: the first nlds in LDS,
+// the rest in memory.
 template <typename T>
-__global__ __launch_bounds__(LINE_THREADS) void k_line_batch(const BatchEntry *__restrict__ ents, int nlaunch)
+__global__ __launch_bounds__(LINE_THREADS) void k_line_batch(const BatchEntry *__restrict__ ents, int nlds, int nlaunch)
 {
     const BatchEntry *e = ents + blockIdx.x;
-    line_body<T>((T *)e->state, e->gp, e->ctrl, -1, 0.0, 0.0, nlaunch, reinterpret_cast<T *>(line_shared));
+    T *const lds = reinterpret_cast<T *>(line_shared);
+    if ((int)blockIdx.x < nlds)
+        line_body<T, true>((T *)e->state, nullptr, e->gp, e->ctrl, -1, 0.0, 0.0, nlaunch, lds);
+    else
+        line_body<T, false>((T *)e->state, (T *)e->half, e->gp, e->ctrl, -1, 0.0, 0.0, nlaunch, lds);
 }
 
 }  // namespace ppml
