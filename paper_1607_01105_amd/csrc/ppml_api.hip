@@ -52,9 +52,15 @@ constexpr int NTILE[4] = {0, 3, 4, 4};
 constexpr int TILE_X[4][4] = {{0, 0, 0, 0}, {256, 128, 64, 0}, {32, 64, 16, 32}, {32, 64, 16, 32}};
 constexpr int TILE_Y[4][4] = {{0, 0, 0, 0}, {1, 1, 1, 0}, {8, 4, 16, 4}, {8, 4, 16, 4}};
 
-// Calls f(Tile<tx, ty>{}) for tile shape v of dimensionality NDIM (the
-// tables above, spelled out as template arguments).
-template <int NDIM, typename F> void with_tile(int v, F &&f)
+// Tile shape that index v stands for in launches.  FP64 3-D launches take 16x16
+// for the default: its Eulerian kernel fits a CU's LDS three times where 32x8
+// fits twice (us per step, 32x8 / 16x16: 512x512x64 2665 / 2340, 192^3 1177 /
+// 1084, 131x97x75 226 / 196, 64^3 75 / 72; 200x40x120 the other way, 195 / 203).
+int launch_tile(int ndim, int prec, int v) { return ndim == 3 && prec == PPML_FP64 && v == 0 ? 2 : v; }
+
+// Calls f(Tile<tx, ty>{}) for launch tile v of dimensionality NDIM (the tables
+// above, spelled out as template arguments).
+template <int NDIM, typename T, typename F> void with_tile(int v, F &&f)
 {
     if constexpr (NDIM == 1) {
         switch (v) {
@@ -67,7 +73,10 @@ template <int NDIM, typename F> void with_tile(int v, F &&f)
         case 1: f(Tile<64, 4>{}); break;
         case 2: f(Tile<16, 16>{}); break;
         case 3: f(Tile<32, 4>{}); break;
-        default: f(Tile<32, 8>{}); break;
+        default:
+            if constexpr (NDIM == 3 && sizeof(T) == 8) f(Tile<16, 16>{});
+            else f(Tile<32, 8>{});
+            break;
         }
     }
 }
@@ -301,7 +310,7 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
         });
         if (ev) (void)hipEventRecord(ev[3], g->stream);
     } else {
-        with_tile<NDIM>(g->d.tile, [&](auto tl) {
+        with_tile<NDIM, T>(launch_tile(NDIM, g->d.prec, g->d.tile), [&](auto tl) {
             using TL = decltype(tl);
             const GridParams &ge = g->gpE;
             const GridParams &gl = g->gpL;
@@ -588,7 +597,7 @@ template <typename T> void stage_slots(int device, int tile, int xf, long long &
 {
     int cus = 0, be = 0, bl = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
-    with_tile<3>(tile, [&](auto tl) {
+    with_tile<3, T>(launch_tile(3, sizeof(T) == 8 ? PPML_FP64 : PPML_FP32, tile), [&](auto tl) {
         using TL = decltype(tl);
         hipError_t e =
             xf == 2   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&be, k_euler<T, 3, TL::tx, TL::ty, 2>, TL::nt, 0)
@@ -647,6 +656,7 @@ void set_tiling(GridParams &gp, int ndim, int prec, int v)
         set_rows(gp, sheet_rows({&gp}, prec));
         return;
     }
+    v = launch_tile(ndim, prec, v);
     const int tx = TILE_X[ndim][v], ty = TILE_Y[ndim][v];
     gp.tiles[0] = (gp.n[0] + tx - 1) / tx;
     gp.tiles[1] = ndim >= 2 ? (gp.n[1] + ty - 1) / ty : 1;
@@ -1506,7 +1516,7 @@ template <typename T, int NDIM> void batch_stage(ppml_batch *b, bool lagr, hipSt
             else k_euler_sheet_batch<T, R><<<b->gtiles[2], SHEET_THREADS, 0, st>>>(e, first, b->gn[2]);
         });
     } else {
-        with_tile<NDIM>(b->tile[NDIM], [&](auto tl) {
+        with_tile<NDIM, T>(launch_tile(NDIM, b->prec, b->tile[NDIM]), [&](auto tl) {
             using TL = decltype(tl);
             const BatchEntry *e = b->d_ents + b->goff[NDIM];
             const int *first = b->d_first + b->goff[NDIM];

@@ -245,6 +245,34 @@ __device__ __forceinline__ void publish_max(Ctrl *ctrl, int mslots, int set, int
         atomicMax(max_slot(ctrl, mslots, set, i) + threadIdx.x, (unsigned long long)__double_as_longlong((double)v));
 }
 
+// The step, published by the lead work group of an Eulerian launch for the
+// Lagrangian kernel; a no-op step (tau = 0) leaves the state, its maxima and the
+// time unchanged.
+__device__ __forceinline__ void publish_step(Ctrl *ctrl, const GridParams &gp, double tau_d)
+{
+    const int s = ctrl->slot_cur;
+    if (threadIdx.x == 0) {
+        ctrl->slot_l = s;
+        ctrl->tau = tau_d > 0.0 ? tau_d : 0.0;
+    }
+    if (tau_d > 0.0 && (int)threadIdx.x < gp.mslots) {
+        unsigned long long *p = max_slot(ctrl, gp.mslots, s ^ 1, threadIdx.x);
+        p[0] = 0ull;
+        p[1] = 0ull;
+    }
+}
+
+// The step's end, by one thread of a Lagrangian launch; sl: the set of maxima
+// the step started from.
+__device__ __forceinline__ void advance_step(Ctrl *ctrl, double tau_d, int sl)
+{
+    ctrl->t = ctrl->t + tau_d;
+    ctrl->dt_last = tau_d;
+    ctrl->steps = ctrl->steps + 1;
+    ctrl->steps_left = ctrl->steps_left - 1;
+    ctrl->slot_cur = sl ^ 1;
+}
+
 // The current maxima into the control block, for the host.
 __global__ __launch_bounds__(64) void k_fold_max(Ctrl *ctrl, int mslots)
 {
@@ -405,20 +433,7 @@ __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restric
     const long long N = gp.ncell;
 
     const double tau_d = uniform(compute_tau(ctrl, gp));
-    if (lead) {
-        // publish the step for the Lagrangian kernel; a no-op step (tau = 0)
-        // leaves the state, its maxima and the time unchanged
-        const int s = ctrl->slot_cur;
-        if (tid == 0) {
-            ctrl->slot_l = s;
-            ctrl->tau = tau_d > 0.0 ? tau_d : 0.0;
-        }
-        if (tau_d > 0.0 && tid < gp.mslots) {
-            unsigned long long *p = max_slot(ctrl, gp.mslots, s ^ 1, tid);
-            p[0] = 0ull;
-            p[1] = 0ull;
-        }
-    }
+    if (lead) publish_step(ctrl, gp, tau_d);
     if (!(tau_d > 0.0)) return;
 
     const T gam = uniform((T)gp.gs);
@@ -448,14 +463,6 @@ __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restric
         z1 = z0 + gp.cz < nz ? z0 + gp.cz : nz;
     }
 
-    // per-field base pointers (uniform) and 32-bit cell offsets
-    const T *Uf[NF];
-    T *Wf[NF];
-#pragma unroll
-    for (int f = 0; f < NF; f++) {
-        Uf[f] = U + (size_t)f * (size_t)N;
-        Wf[f] = Wst + (size_t)f * (size_t)N;
-    }
     const int plane = nx * ny;
     const int own_off = cy_ * nx + cx_;
 
@@ -514,9 +521,9 @@ __device__ __forceinline__ void euler_body(const T *__restrict__ U, T *__restric
         int fzn = 0;
         auto load_column = [&](const int mm) {
             const int c = map_index(mm, nz, gp.bc_lo[2], gp.bc_hi[2], fzn) * plane + own_off;
-            zn0 = Uf[0][c];
-            zn1 = Uf[3][c];
-            zn2 = Uf[5][c];
+            zn0 = U[c];
+            zn1 = U[(size_t)3 * (size_t)N + c];
+            zn2 = U[(size_t)5 * (size_t)N + c];
         };
         Profile<T> pvB = pv_prev, ppB = pp_prev;
         auto plane_step = [&](const int m, Profile<T> &pv_prev, Profile<T> &pp_prev, Profile<T> &pv_next,
@@ -625,13 +632,7 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
     if (!(tau_d > 0.0)) return;
     const int tid = threadIdx.x;
     const int sl = ctrl->slot_l;
-    if (lead) {
-        ctrl->t = ctrl->t + tau_d;
-        ctrl->dt_last = tau_d;
-        ctrl->steps = ctrl->steps + 1;
-        ctrl->steps_left = ctrl->steps_left - 1;
-        ctrl->slot_cur = sl ^ 1;
-    }
+    if (lead) advance_step(ctrl, tau_d, sl);
     const int tx = tid % TX, ty = tid / TX;
     const int wv = wave_id(), ln = tid & 63;  // the wave (scalar) and the lane
     const int x0 = bx * TX, y0 = by * TY;
@@ -660,10 +661,6 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
         z1 = z0 + gp.cz < nz ? z0 + gp.cz : nz;
     }
 
-    // per-field base pointers (uniform) and 32-bit cell offsets
-    const T *Wf[NF];
-#pragma unroll
-    for (int f = 0; f < NF; f++) Wf[f] = Wst + (size_t)f * (size_t)N;
     const int plane = nx * ny;
     const int own_off = cy_ * nx + cx_;
 
@@ -737,7 +734,7 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
     // cross tile of plane kk, every field, from memory into the LDS buffer of
     // plane kk: each wave fills 64 consecutive tile slots per field, lanes
     // without a cross cell do not transfer
-    auto dma_cross = [&](int kk) {
+    auto dma_cross = [&](int kk, size_t Nf) {
         T (*dst)[PS] = s_f[kk & 1];
 #pragma unroll
         for (int r = 0; r < RC; r++) {
@@ -746,11 +743,11 @@ __device__ __forceinline__ void lagr_body(const T *__restrict__ Wst, T *__restri
             const int wbase = r * NT + wv * 64;  // the wave's first slot (scalar)
 #pragma unroll
             for (int f = 0; f < NF; f++)
-                __builtin_amdgcn_global_load_lds((const void *)(Wf[f] + c),
+                __builtin_amdgcn_global_load_lds((const void *)(Wst + f * Nf + c),
                                                  (__attribute__((address_space(3))) void *)&dst[f][wbase], 4, 0, 0);
         }
     };
-    if constexpr (PIPE) dma_cross(z0);
+    if constexpr (PIPE) dma_cross(z0, (size_t)N);
     // the cross tile of plane kk arrived by transfer: once this wave's
     // transfers have landed, each thread mirrors the normal momenta at
     // reflecting faces and writes the state of inflow faces into the slots

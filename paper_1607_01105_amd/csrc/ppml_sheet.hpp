@@ -121,20 +121,7 @@ __device__ __forceinline__ void euler_sheet(const T *__restrict__ U, T *__restri
             sheet_load<T, 0x15 | (0x1F << 5)>(gp, col, j0 - GH + i, i >= GH && i < R + GH, u[i]);
     }
     const double tau_d = uniform(compute_tau(ctrl, gp));
-    if (lead) {
-        // publish the step for the Lagrangian kernel; a no-op step (tau = 0)
-        // leaves the state, its maxima and the time unchanged
-        const int s = ctrl->slot_cur;
-        if (threadIdx.x == 0) {
-            ctrl->slot_l = s;
-            ctrl->tau = tau_d > 0.0 ? tau_d : 0.0;
-        }
-        if (tau_d > 0.0 && (int)threadIdx.x < gp.mslots) {
-            unsigned long long *p = max_slot(ctrl, gp.mslots, s ^ 1, threadIdx.x);
-            p[0] = 0ull;
-            p[1] = 0ull;
-        }
-    }
+    if (lead) publish_step(ctrl, gp, tau_d);
     if (!(tau_d > 0.0) || !strip) return;
     const T gam = uniform((T)gp.gs), gm1 = uniform((T)gp.pb), prho = uniform((T)gp.pa), tau = uniform((T)tau_d);
     const T hx = uniform((T)gp.h[0]), hy = uniform((T)gp.h[1]);
@@ -235,13 +222,7 @@ __device__ __forceinline__ void lagr_sheet(const T *__restrict__ Wst, T *__restr
     const double tau_d = ctrl->tau;
     if (!(tau_d > 0.0)) return;
     const int sl = ctrl->slot_l;
-    if (lead) {
-        ctrl->t = ctrl->t + tau_d;
-        ctrl->dt_last = tau_d;
-        ctrl->steps = ctrl->steps + 1;
-        ctrl->steps_left = ctrl->steps_left - 1;
-        ctrl->slot_cur = sl ^ 1;
-    }
+    if (lead) advance_step(ctrl, tau_d, sl);
     T vmax = T(0), cmax = T(0);
     if (strip) {
         const T gam = uniform((T)gp.gs), gm1 = uniform((T)gp.pb), prho = uniform((T)gp.pa), tau = uniform((T)tau_d);
