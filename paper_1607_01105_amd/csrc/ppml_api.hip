@@ -20,6 +20,7 @@
 #include "ppml_kernels.hpp"
 #include "ppml_line.hpp"
 #include "ppml_sheet.hpp"
+#include "ppml_brick.hpp"
 
 using namespace ppml;
 
@@ -251,6 +252,8 @@ struct ppml_grid {
     ppml_desc d;
     GridParams gp;         // batch launches and the per-cell kernels
     GridParams gpE, gpL;   // solo launches of the two stage kernels (own z chunks)
+    GridParams gpB;        // solo launches of the row kernels of small 3-D grids
+    bool brick;            // the grid takes those
     hipStream_t stream;
     int device;
     void *state;
@@ -284,6 +287,13 @@ int work_groups(const GridParams &gp)
     return gp.ndim == 2 ? (t + per - 1) / per : t;
 }
 
+// ... of a launch of the row kernels: one per four rows' strips.
+int brick_groups(const GridParams &gp)
+{
+    constexpr int per = SHEET_THREADS / 64;
+    return (int)(((long long)gp.tiles[0] * gp.n[1] * gp.n[2] + per - 1) / per);
+}
+
 template <typename T> void launch_speeds(ppml_grid *g)
 {
     const T *U = (const T *)g->state;
@@ -308,6 +318,16 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
             if (ev) (void)hipEventRecord(ev[2], g->stream);
             k_lagr_sheet<T, R><<<work_groups(g->gp), SHEET_THREADS, 0, g->stream>>>(W, Us, g->gp, g->ctrl);
         });
+        if (ev) (void)hipEventRecord(ev[3], g->stream);
+    } else if (NDIM == 3 && g->brick) {
+        const GridParams &gp = g->gpB;
+        const int nb = brick_groups(gp);
+        if (ev) (void)hipEventRecord(ev[1], g->stream);
+        if (gp.potential == POT_HALO) k_euler_brick<T, 2><<<nb, SHEET_THREADS, 0, g->stream>>>(U, W, gp, g->ctrl);
+        else if (gp.self_grav) k_euler_brick<T, 1><<<nb, SHEET_THREADS, 0, g->stream>>>(U, W, gp, g->ctrl);
+        else k_euler_brick<T, 0><<<nb, SHEET_THREADS, 0, g->stream>>>(U, W, gp, g->ctrl);
+        if (ev) (void)hipEventRecord(ev[2], g->stream);
+        k_lagr_brick<T><<<nb, SHEET_THREADS, 0, g->stream>>>(W, Us, gp, g->ctrl);
         if (ev) (void)hipEventRecord(ev[3], g->stream);
     } else {
         with_tile<NDIM, T>(launch_tile(NDIM, g->d.prec, g->d.tile), [&](auto tl) {
@@ -818,6 +838,19 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
     return PPML_OK;
 }
 
+// Whether a 3-D grid alone takes the row kernels: up to four waves (row strips)
+// per SIMD, the default tile shape (the others name the marching kernels' work
+// groups) and no inflow face, whose ghost states the row kernels do not form.
+// us per step, march / rows: FP32 24^3 30 / 20, 40x60x30 (1800 waves) 40 / 31,
+// 58x27x148 (3996) 54 / 39, 64^3 (8192) 48 / 62, 100^3 (20000) 105 / 115; FP64
+// 24^3 42 / 30, 40x60x30 56 / 45, 58x27x148 88 / 68, 64^3 71 / 114.
+constexpr long long BRICK_WAVES = 4096;
+bool brick_grid(const ppml_desc *d, const GridParams &gp)
+{
+    return d->ndim == 3 && d->tile == 0 && !gp.any_inflow &&
+           (d->n[0] + SHEET_W - 1) / SHEET_W * d->n[1] * d->n[2] <= BRICK_WAVES;
+}
+
 // Z chunks of the solo stage launches, fitted to the resident work groups of
 // each stage kernel (start-up cost: 3 z-only planes in the Eulerian kernel, 6
 // in the Lagrangian kernel).  After the self-gravity set-up, which selects
@@ -828,6 +861,12 @@ void init_chunks(ppml_grid *g)
     const ppml_desc *d = &g->d;
     g->gpE = gp;
     g->gpL = gp;
+    g->gpB = gp;
+    g->brick = brick_grid(d, gp);
+    if (g->brick) {
+        g->gpB.tiles[0] = (gp.n[0] + SHEET_W - 1) / SHEET_W;
+        return;
+    }
     if (d->ndim == 3) {
         long long se, sl;
         const int xf = gp.potential == POT_HALO ? 2 : (gp.self_grav ? 1 : 0);
