@@ -22,7 +22,8 @@
  *  - Memory: the caller owns all device memory and the HIP stream; the
  *    library borrows the pointers for the lifetime of the grid and owns only
  *    the small opaque host object (and short-lived staging buffers inside
- *    the set/get calls).
+ *    the set/get calls, of which it keeps at most 16 MiB of pinned host memory
+ *    for the next call; those calls use up to eight host threads).
  *  - Device state layout (structure of arrays, x fastest, C order
  *    [z][y][x]): F = 3 + ndim fields of n[0]*n[1]*n[2] values of the storage
  *    type (float for PPML_FP32, double for PPML_FP64), in the order

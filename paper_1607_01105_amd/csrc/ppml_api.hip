@@ -18,6 +18,7 @@
 #include "../../include/ppml.h"
 #include "ppml_gravity.hpp"
 #include "ppml_kernels.hpp"
+#include "ppml_transfer.hpp"
 #include "ppml_line.hpp"
 #include "ppml_sheet.hpp"
 #include "ppml_brick.hpp"
@@ -575,17 +576,39 @@ int finish_set(ppml_grid *g, double t, double rho_mean0)
     return PPML_OK;
 }
 
-bool all_finite_positive(const double *a, long long n)
+// The transfers of ppml_transfer.hpp; their threads and buffers may not be had.
+template <typename T>
+int upload(ppml_grid *g, const double *const *src, int nsrc, T *dst, const char *what)
 {
-    for (long long i = 0; i < n; i++)
-        if (!(a[i] > 0.0) || !std::isfinite(a[i])) return false;
-    return true;
+    hipError_t e;
+    try {
+        e = xfer_upload<T>(g->device, g->stream, src, nsrc, g->gp.ncell, dst);
+    } catch (const std::exception &) {
+        return fail(PPML_ENOMEM, "%s: host allocation failed", what);
+    }
+    return e == hipSuccess ? PPML_OK : fail(PPML_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-bool all_finite(const double *a, long long n)
+template <typename T> int download(ppml_grid *g, const T *src, long long n, double *dst, const char *what)
 {
+    hipError_t e;
+    try {
+        e = xfer_download<T>(g->device, g->stream, src, n, dst);
+    } catch (const std::exception &) {
+        return fail(PPML_ENOMEM, "%s: host allocation failed", what);
+    }
+    return e == hipSuccess ? PPML_OK : fail(PPML_EHIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+bool all_finite(const double *a, long long n, bool positive)
+{
+    try {
+        return xfer_check(a, n, positive);
+    } catch (const std::exception &) {
+        // no memory for the threads' bookkeeping
+    }
     for (long long i = 0; i < n; i++)
-        if (!std::isfinite(a[i])) return false;
+        if (!std::isfinite(a[i]) || (positive && !(a[i] > 0.0))) return false;
     return true;
 }
 
@@ -954,38 +977,25 @@ int ppml_set_primitive(ppml_grid *g, const double *rho, const double *vx, const 
     if ((rc = settle(g))) return rc;
     if (!rho || !p) return fail(PPML_EINVAL, "rho and p are required");
     const long long N = g->gp.ncell;
-    if (!all_finite_positive(rho, N)) return fail(PPML_EINVAL, "rho must be finite and > 0");
-    if (!all_finite_positive(p, N)) return fail(PPML_EINVAL, "p must be finite and > 0");
+    if (!all_finite(rho, N, true)) return fail(PPML_EINVAL, "rho must be finite and > 0");
+    if (!all_finite(p, N, true)) return fail(PPML_EINVAL, "p must be finite and > 0");
     const double *v[3] = {vx, vy, vz};
     for (int a = 0; a < g->d.ndim; a++)
-        if (v[a] && !all_finite(v[a], N)) return fail(PPML_EINVAL, "velocity %d has non-finite values", a);
+        if (v[a] && !all_finite(v[a], N, false)) return fail(PPML_EINVAL, "velocity %d has non-finite values", a);
     double *prim = nullptr;
     HIPCHK(hipMallocAsync((void **)&prim, (size_t)5 * N * sizeof(double), g->stream));
     const double *src[5] = {rho, vx, vy, vz, p};
-    for (int i = 0; i < 5; i++) {
-        if (src[i]) {
-            hipError_t e = hipMemcpyAsync(prim + (size_t)i * N, src[i], N * sizeof(double), hipMemcpyHostToDevice,
-                                          g->stream);
-            if (e != hipSuccess) {
-                (void)hipFreeAsync(prim, g->stream);
-                return fail(PPML_EHIP, "copy of primitive %d: %s", i, hipGetErrorString(e));
-            }
-        } else {
-            hipError_t e = hipMemsetAsync(prim + (size_t)i * N, 0, N * sizeof(double), g->stream);
-            if (e != hipSuccess) {
-                (void)hipFreeAsync(prim, g->stream);
-                return fail(PPML_EHIP, "hipMemsetAsync: %s", hipGetErrorString(e));
-            }
-        }
+    rc = upload<double>(g, src, 5, prim, "copy of the primitives");
+    hipError_t e = hipSuccess;
+    if (rc == PPML_OK) {
+        int nb = (int)std::min<long long>(4096, (N + 255) / 256);
+        if (g->d.prec == PPML_FP64) k_prim_to_cons<double><<<nb, 256, 0, g->stream>>>(prim, (double *)g->state, g->gp);
+        else k_prim_to_cons<float><<<nb, 256, 0, g->stream>>>(prim, (float *)g->state, g->gp);
+        e = hipGetLastError();
     }
-    int nb = (int)std::min<long long>(4096, (N + 255) / 256);
-    if (g->d.prec == PPML_FP64) k_prim_to_cons<double><<<nb, 256, 0, g->stream>>>(prim, (double *)g->state, g->gp);
-    else k_prim_to_cons<float><<<nb, 256, 0, g->stream>>>(prim, (float *)g->state, g->gp);
-    hipError_t e = hipGetLastError();
     (void)hipFreeAsync(prim, g->stream);
-    hipError_t e2 = hipStreamSynchronize(g->stream);
-    if (e != hipSuccess || e2 != hipSuccess)
-        return fail(PPML_EHIP, "prim_to_cons: %s", hipGetErrorString(e != hipSuccess ? e : e2));
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(PPML_EHIP, "prim_to_cons: %s", hipGetErrorString(e));
     return finish_set(g, 0.0, 0.0);
 }
 
@@ -997,41 +1007,22 @@ int ppml_set_conserved(ppml_grid *g, const double *const *f, double rho_mean0, d
     if (!f || !f[PPML_RHO] || !f[PPML_ETOT] || !f[PPML_EINT]) return fail(PPML_EINVAL, "rho, Et and e are required");
     const long long N = g->gp.ncell;
     const int nd = g->d.ndim;
-    if (!all_finite_positive(f[PPML_RHO], N)) return fail(PPML_EINVAL, "rho must be finite and > 0");
-    if (!all_finite_positive(f[PPML_EINT], N)) return fail(PPML_EINVAL, "rho*eps must be finite and > 0");
-    if (!all_finite(f[PPML_ETOT], N)) return fail(PPML_EINVAL, "rho*E must be finite");
+    if (!all_finite(f[PPML_RHO], N, true)) return fail(PPML_EINVAL, "rho must be finite and > 0");
+    if (!all_finite(f[PPML_EINT], N, true)) return fail(PPML_EINVAL, "rho*eps must be finite and > 0");
+    if (!all_finite(f[PPML_ETOT], N, false)) return fail(PPML_EINVAL, "rho*E must be finite");
     if (!std::isfinite(t) || t < 0.0) return fail(PPML_EINVAL, "t must be finite and >= 0");
-    double *tmp = nullptr;
-    HIPCHK(hipMallocAsync((void **)&tmp, (size_t)N * sizeof(double), g->stream));
-    int nb = (int)std::min<long long>(4096, (N + 255) / 256);
     // stored field s <- ppml_field
-    int nfs = nfields(&g->d);
-    for (int s = 0; s < nfs; s++) {
-        int fld = s == 0 ? PPML_RHO : (s <= nd ? s : (s == nd + 1 ? PPML_ETOT : PPML_EINT));
-        hipError_t e;
-        if (f[fld]) {
-            if (!all_finite(f[fld], N)) {
-                (void)hipFreeAsync(tmp, g->stream);
-                return fail(PPML_EINVAL, "field %d has non-finite values", fld);
-            }
-            e = hipMemcpyAsync(tmp, f[fld], N * sizeof(double), hipMemcpyHostToDevice, g->stream);
-        } else {
-            e = hipMemsetAsync(tmp, 0, N * sizeof(double), g->stream);
-        }
-        if (e == hipSuccess) {
-            if (g->d.prec == PPML_FP64)
-                k_from_double<double><<<nb, 256, 0, g->stream>>>(tmp, (double *)g->state + (size_t)s * N, N);
-            else
-                k_from_double<float><<<nb, 256, 0, g->stream>>>(tmp, (float *)g->state + (size_t)s * N, N);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-        if (e != hipSuccess) {
-            (void)hipFreeAsync(tmp, g->stream);
-            return fail(PPML_EHIP, "set_conserved: %s", hipGetErrorString(e));
-        }
+    const int nfs = nfields(&g->d);
+    const double *src[6];
+    for (int q = 0; q < nfs; q++) {
+        const int fld = q == 0 ? PPML_RHO : (q <= nd ? q : (q == nd + 1 ? PPML_ETOT : PPML_EINT));
+        src[q] = f[fld];
+        if (q >= 1 && q <= nd && src[q] && !all_finite(src[q], N, false))
+            return fail(PPML_EINVAL, "field %d has non-finite values", fld);
     }
-    (void)hipFreeAsync(tmp, g->stream);
+    rc = g->d.prec == PPML_FP64 ? upload<double>(g, src, nfs, (double *)g->state, "set_conserved")
+                                : upload<float>(g, src, nfs, (float *)g->state, "set_conserved");
+    if (rc) return rc;
     return finish_set(g, t, rho_mean0);
 }
 
@@ -1271,19 +1262,8 @@ int ppml_get_conserved(ppml_grid *g, int32_t field, double *host_out)
     }
     if (s < 0) return fail(PPML_EINVAL, "field %d is not stored for ndim=%d", field, nd);
     const long long N = g->gp.ncell;
-    double *tmp = nullptr;
-    HIPCHK(hipMallocAsync((void **)&tmp, (size_t)N * sizeof(double), g->stream));
-    int nb = (int)std::min<long long>(4096, (N + 255) / 256);
-    if (g->d.prec == PPML_FP64)
-        k_to_double<double><<<nb, 256, 0, g->stream>>>((const double *)g->state + (size_t)s * N, tmp, N);
-    else
-        k_to_double<float><<<nb, 256, 0, g->stream>>>((const float *)g->state + (size_t)s * N, tmp, N);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(host_out, tmp, N * sizeof(double), hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    (void)hipFreeAsync(tmp, g->stream);
-    if (e != hipSuccess) return fail(PPML_EHIP, "get_conserved: %s", hipGetErrorString(e));
-    return PPML_OK;
+    return g->d.prec == PPML_FP64 ? download<double>(g, (const double *)g->state + (size_t)s * N, N, host_out, "get_conserved")
+                                  : download<float>(g, (const float *)g->state + (size_t)s * N, N, host_out, "get_conserved");
 }
 
 int ppml_totals(ppml_grid *g, double out[6])
@@ -1366,17 +1346,8 @@ int ppml_get_potential(ppml_grid *g, double *host_out)
     rc = g->d.prec == PPML_FP64 ? launch_gravity<double>(g) : launch_gravity<float>(g);
     if (rc) return rc;
     const long long np = (long long)(g->gp.n[0] + 2) * (g->gp.n[1] + 2) * (g->gp.n[2] + 2);
-    double *tmp = nullptr;
-    HIPCHK(hipMallocAsync((void **)&tmp, (size_t)np * sizeof(double), g->stream));
-    int nb = (int)std::min<long long>(4096, (np + 255) / 256);
-    if (g->d.prec == PPML_FP64) k_to_double<double><<<nb, 256, 0, g->stream>>>((const double *)g->phi, tmp, np);
-    else k_to_double<float><<<nb, 256, 0, g->stream>>>((const float *)g->phi, tmp, np);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(host_out, tmp, np * sizeof(double), hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    (void)hipFreeAsync(tmp, g->stream);
-    if (e != hipSuccess) return fail(PPML_EHIP, "get_potential: %s", hipGetErrorString(e));
-    return PPML_OK;
+    return g->d.prec == PPML_FP64 ? download<double>(g, (const double *)g->phi, np, host_out, "get_potential")
+                                  : download<float>(g, (const float *)g->phi, np, host_out, "get_potential");
 }
 
 int ppml_destroy(ppml_grid *g)

@@ -96,18 +96,6 @@ __global__ void k_prim_to_cons(const double *__restrict__ prim, T *__restrict__ 
     }
 }
 
-template <typename T> __global__ void k_from_double(const double *__restrict__ src, T *__restrict__ dst, long long n)
-{
-    for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += (long long)gridDim.x * blockDim.x)
-        dst[c] = (T)src[c];
-}
-
-template <typename T> __global__ void k_to_double(const T *__restrict__ src, double *__restrict__ dst, long long n)
-{
-    for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += (long long)gridDim.x * blockDim.x)
-        dst[c] = (double)src[c];
-}
-
 // Control block and maxima slots of a freshly set state: time t, vacuum
 // reference density rho_mean0 (<= 0: left for the totals kernel to fill in).
 __global__ __launch_bounds__(2 * MSLOT_MAX) void k_ctrl_reset(Ctrl *ctrl, int mslots, double t, double rho_mean0)
