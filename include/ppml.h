@@ -14,7 +14,7 @@
  * with the 9-point transverse velocity; Sec. 2.3) + total-energy correction
  * (Sec. 2.4), optionally preceded by the self-gravity potential solve
  * (Sec. 2.5).  Every step runs in HIP kernels on the caller's stream (the
- * self-gravity transforms as rocBLAS GEMMs on the same stream).
+ * self-gravity transforms of long axes as rocBLAS GEMMs on the same stream).
  *
  * Conventions shared by every function:
  *  - Return value: PPML_OK (0) or a negative ppml_status.  Nothing throws
@@ -132,9 +132,10 @@ typedef struct {
  * stencil's eigenvalues and the inverse transforms.  The force terms of
  * eqs. (2)-(3) then use the central difference of the potential across each
  * cell, added to any fixed potential's gradient.  The scratch area grows by
- * the potential, two work arrays of the grid's size, the shell terms of the
- * outer layer of cells and the sine tables (see ppml_scratch_bytes).  Grids with self-gravity step alone, not in a
- * batch. */
+ * the potential, a work array of the grid's size (two with an axis of more
+ * than 512 cells in FP32, 256 in FP64), the shell terms of the outer layer of
+ * cells and the sine tables (see ppml_scratch_bytes).  Grids with
+ * self-gravity step alone, not in a batch. */
 
 /* Work-group tile shapes of the stage kernels for grids of ndim dimensions:
  * ppml_tile_count returns how many there are (>= 1) or PPML_EINVAL;

@@ -41,7 +41,7 @@ def _command(out: str, exact: bool) -> list[str]:
         # alone, and every kernel that inlines a formula gives the same bits
         # (solo and batched launches, tile shapes, rows per wave)
         flags += ["-fno-hip-fp32-correctly-rounded-divide-sqrt", "-fgpu-flush-denormals-to-zero", "-ffp-contract=on"]
-    # rocBLAS runs the GEMMs of the self-gravity sine transforms
+    # rocBLAS runs the GEMMs of the self-gravity sine transforms of long axes
     return [HIPCC, *flags, SRC, "-o", out + ".tmp", "-L/opt/rocm/lib", "-lrocblas", "-Wl,-rpath,/opt/rocm/lib"]
 
 

@@ -17,6 +17,7 @@
 
 #include "../../include/ppml.h"
 #include "ppml_gravity.hpp"
+#include "ppml_sine.hpp"
 #include "ppml_kernels.hpp"
 #include "ppml_transfer.hpp"
 #include "ppml_line.hpp"
@@ -205,6 +206,28 @@ struct ScratchLayout {
 // Moment reduction of the self-gravity solve: fixed block count (fixed order).
 int grav_blocks(long long n) { return (int)std::min<long long>(1024, (n + 2047) / 2048 > 0 ? (n + 2047) / 2048 : 1); }
 
+// The kernels of ppml_sine.hpp hold a line's two halves in registers (in the
+// z pass its results too): up to SINE_TILES blocks of 16 a half, 512 cells in
+// FP32 and 256 in FP64, where the z pass fills the 512 registers of a lane.
+// A grid with a longer axis takes library products.
+template <typename T> constexpr int SINE_TILES = sizeof(T) == 4 ? 16 : 8;
+
+bool sine_kernels(const ppml_desc *d)
+{
+    const int most = 16 * (d->prec == PPML_FP64 ? SINE_TILES<double> : SINE_TILES<float>);
+    for (int a = 0; a < 3; a++)
+        if (grav_no(d->n[a]) > most) return false;
+    return true;
+}
+
+size_t sine_table_bytes(const ppml_desc *d, int axis)
+{
+    const int n = d->n[axis];
+    if (!sine_kernels(d)) return (size_t)n * n * elem(d);
+    return d->prec == PPML_FP64 ? sine_table_count<double>(n) * sizeof(double)
+                                : sine_table_count<float>(n) * sizeof(float);
+}
+
 ScratchLayout layout(const ppml_desc *d)
 {
     ScratchLayout L;
@@ -225,13 +248,13 @@ ScratchLayout layout(const ppml_desc *d)
         L.wx = sz;
         sz += align_up(n0 * n1 * n2 * e);
         L.wy = sz;
-        sz += align_up(n0 * n1 * n2 * e);
+        if (!sine_kernels(d)) sz += align_up(n0 * n1 * n2 * e);  // the passes of ppml_sine.hpp run in place
         L.sx = sz;
-        sz += align_up(n0 * n0 * e);
+        sz += align_up(sine_table_bytes(d, 0));
         L.sy = sz;
-        sz += align_up(n1 * n1 * e);
+        sz += align_up(sine_table_bytes(d, 1));
         L.sz = sz;
-        sz += align_up(n2 * n2 * e);
+        sz += align_up(sine_table_bytes(d, 2));
         L.fx = sz;
         sz += align_up(n0 * sizeof(double));
         L.fy = sz;
@@ -454,6 +477,58 @@ template <typename T> int sine_transform(ppml_grid *g, int axis, bool inverse, c
     return PPML_OK;
 }
 
+constexpr int SINE_BLOCKS = 256;  // a block per CU
+
+template <typename T, int MT, int KIND>
+int sine_launch(ppml_grid *g, const T *src, T *dst, const T *S, int nlines)
+{
+    using Shape = SineShape<T, MT, KIND>;
+    constexpr int lds = Shape::CT * Shape::TILE;
+    if (lds > 64 * 1024)
+        HIPCHK(hipFuncSetAttribute((const void *)k_sine<T, MT, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    const int tiles = (nlines + 15) / 16;
+    const int waves = std::max(1, std::min(Shape::WAVES, (tiles + SINE_BLOCKS - 1) / SINE_BLOCKS));
+    const int blocks = std::min(SINE_BLOCKS, (tiles + waves - 1) / waves);
+    const SineArgs args = {g->grav_coef, g->grav_norm};
+    k_sine<T, MT, KIND><<<blocks, 64 * waves, lds, g->stream>>>(src, dst, S, (const T *)g->gedge, g->fx, g->fy, g->fz,
+                                                                g->gp, args);
+    return PPML_OK;
+}
+
+template <typename T, int KIND> int sine_pass(ppml_grid *g, const T *src, T *dst)
+{
+    constexpr int axis = KIND == SINE_Z ? 2 : KIND == SINE_Y_FWD || KIND == SINE_Y_INV ? 1 : 0;
+    const int *n = g->gp.n;
+    const T *S = (const T *)(axis == 0 ? g->sx : axis == 1 ? g->sy : g->sz);
+    const int nl = axis == 0 ? n[1] * n[2] : axis == 1 ? n[0] * n[2] : n[0] * n[1];
+    switch (sine_tiles(n[axis])) {
+    case 1: return sine_launch<T, 1, KIND>(g, src, dst, S, nl);
+    case 2: return sine_launch<T, 2, KIND>(g, src, dst, S, nl);
+    case 3: return sine_launch<T, 3, KIND>(g, src, dst, S, nl);
+    case 4: return sine_launch<T, 4, KIND>(g, src, dst, S, nl);
+    case 5: return sine_launch<T, 5, KIND>(g, src, dst, S, nl);
+    case 6: return sine_launch<T, 6, KIND>(g, src, dst, S, nl);
+    case 7: return sine_launch<T, 7, KIND>(g, src, dst, S, nl);
+    case 8: return sine_launch<T, 8, KIND>(g, src, dst, S, nl);
+    }
+    if constexpr (SINE_TILES<T> == 16) {
+        if (sine_tiles(n[axis]) == 12) return sine_launch<T, 12, KIND>(g, src, dst, S, nl);
+        return sine_launch<T, 16, KIND>(g, src, dst, S, nl);
+    }
+    return fail(PPML_EINVAL, "sine transform of %d cells", n[axis]);
+}
+
+template <typename T> void sine_tables(ppml_grid *g)
+{
+    void *S[3] = {g->sx, g->sy, g->sz};
+    double *f[3] = {g->fx, g->fy, g->fz};
+    for (int a = 0; a < 3; a++) {
+        const int n = g->gp.n[a];
+        const long long m = std::max<long long>(sine_table_count<T>(n), n);
+        k_sine_table<T><<<(unsigned)((m + 255) / 256), 256, 0, g->stream>>>((T *)S[a], f[a], n);
+    }
+}
+
 // The self-gravity potential of the current state into g->phi (Sec. 2.5).
 template <typename T> int launch_gravity(ppml_grid *g)
 {
@@ -476,6 +551,16 @@ template <typename T> int launch_gravity(ppml_grid *g)
     T *E = (T *)g->gedge;
     const long long nedge = grav_edge_cells(n0, n1, n2);
     k_grav_edge_terms<T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(phi, gp, E);
+    if (sine_kernels(&g->d)) {
+        int rc;
+        if ((rc = sine_pass<T, SINE_X_FWD>(g, rho, X))) return rc;
+        if ((rc = sine_pass<T, SINE_Y_FWD>(g, X, X))) return rc;
+        if ((rc = sine_pass<T, SINE_Z>(g, X, X))) return rc;
+        if ((rc = sine_pass<T, SINE_Y_INV>(g, X, X))) return rc;
+        if ((rc = sine_pass<T, SINE_X_INV>(g, X, phi))) return rc;
+        HIPCHK(hipGetLastError());
+        return PPML_OK;
+    }
     const long long nrep = (long long)grav_no(n0) * grav_no(n1) * grav_no(n2);
     const unsigned nbr = (unsigned)((nrep + 255) / 256);
     k_grav_butterfly<T><<<nbr, 256, 0, g->stream>>>(rho, E, g->grav_coef, Y, gp);
@@ -939,27 +1024,32 @@ int ppml_create(const ppml_desc *d, void *state_dev, void *scratch_dev, void *hi
         const double h = gp.h[0];
         g->grav_coef = 4.0 * M_PI * d->grav_G * h * h;
         g->grav_norm = (2.0 / (double)(gp.n[0] + 1)) * (2.0 / (double)(gp.n[1] + 1)) * (2.0 / (double)(gp.n[2] + 1));
-        if (rocblas_create_handle(&g->blas) != rocblas_status_success) {
-            delete g;
-            return fail(PPML_EHIP, "rocblas_create_handle failed");
+        if (sine_kernels(d)) {
+            if (d->prec == PPML_FP64) sine_tables<double>(g);
+            else sine_tables<float>(g);
+        } else {
+            if (rocblas_create_handle(&g->blas) != rocblas_status_success) {
+                delete g;
+                return fail(PPML_EHIP, "rocblas_create_handle failed");
+            }
+            if (rocblas_set_stream(g->blas, g->stream) != rocblas_status_success) {
+                rocblas_destroy_handle(g->blas);
+                delete g;
+                return fail(PPML_EHIP, "rocblas_set_stream failed");
+            }
+            const long long nt = grav_table_count(gp.n[0]) + grav_table_count(gp.n[1]) + grav_table_count(gp.n[2]);
+            const unsigned nbt = (unsigned)((nt + 255) / 256);
+            if (d->prec == PPML_FP64)
+                k_grav_tables<double><<<nbt, 256, 0, g->stream>>>((double *)g->sx, (double *)g->sy, (double *)g->sz,
+                                                                   g->fx, g->fy, g->fz, gp.n[0], gp.n[1], gp.n[2]);
+            else
+                k_grav_tables<float><<<nbt, 256, 0, g->stream>>>((float *)g->sx, (float *)g->sy, (float *)g->sz, g->fx,
+                                                                  g->fy, g->fz, gp.n[0], gp.n[1], gp.n[2]);
         }
-        if (rocblas_set_stream(g->blas, g->stream) != rocblas_status_success) {
-            rocblas_destroy_handle(g->blas);
-            delete g;
-            return fail(PPML_EHIP, "rocblas_set_stream failed");
-        }
-        const long long nt = grav_table_count(gp.n[0]) + grav_table_count(gp.n[1]) + grav_table_count(gp.n[2]);
-        const unsigned nbt = (unsigned)((nt + 255) / 256);
-        if (d->prec == PPML_FP64)
-            k_grav_tables<double><<<nbt, 256, 0, g->stream>>>((double *)g->sx, (double *)g->sy, (double *)g->sz,
-                                                               g->fx, g->fy, g->fz, gp.n[0], gp.n[1], gp.n[2]);
-        else
-            k_grav_tables<float><<<nbt, 256, 0, g->stream>>>((float *)g->sx, (float *)g->sy, (float *)g->sz, g->fx,
-                                                              g->fy, g->fz, gp.n[0], gp.n[1], gp.n[2]);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
         if (e != hipSuccess) {
-            rocblas_destroy_handle(g->blas);
+            if (g->blas) rocblas_destroy_handle(g->blas);
             delete g;
             return fail(PPML_EHIP, "self-gravity tables: %s", hipGetErrorString(e));
         }
@@ -1103,7 +1193,8 @@ int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop)
     HIPCHK(hipGetLastError());  // before a capture attempt clears the last error
     // long calls replay the captured chunk (launch overhead once per
     // STEP_GRAPH steps); not while per-step timing is recorded, nor with
-    // self-gravity (its library GEMMs stay outside captured graphs)
+    // self-gravity (its library GEMMs, on long axes, stay outside captured
+    // graphs)
     int s = 0;
     if (nsteps >= STEP_GRAPH && !timing && !g->gp.self_grav && step_graph(g)) {
         for (; s + STEP_GRAPH <= nsteps; s += STEP_GRAPH) HIPCHK(hipGraphLaunch(g->sexec, g->stream));

@@ -31,7 +31,8 @@
 //      k_grav_unbutterfly undoes the sums and differences into the interior
 //      of the shell-padded potential, which the Eulerian kernel differences.
 // Tables (half-size sine matrices, eigenvalue factors) are built once by
-// k_grav_tables.
+// k_grav_tables.  The kernels of ppml_sine.hpp take the place of steps 4 to 6
+// and of the sums and differences of step 3 on grids whose axes they cover.
 #pragma once
 
 #include "ppml_device.hpp"
@@ -430,6 +431,24 @@ __global__ void k_grav_unbutterfly(const T *__restrict__ Y, T *__restrict__ phi,
                     phi[pad_index(gp, cx[mx], cy[my], cz[mz])] = (T)a[mz][my][mx];
 }
 
+// Amplitude over the eigenvalue -6 (1 - fxy fz) times the inverse
+// transform's factor.  1 - fxy fz is small for the low modes: one rounding.
+template <typename T> __device__ __forceinline__ T grav_amplitude(T v, double fxy, double fz, double norm)
+{
+#ifdef PPML_EXACT
+    const double lam = -6.0 * (1.0 - fxy * fz);
+    return (T)((double)v / lam * norm);
+#else
+    // reciprocal by two Newton steps from the hardware estimate (within an
+    // ulp or two of the division)
+    const double lam = -6.0 * __builtin_fma(-fxy, fz, 1.0);
+    double r = __builtin_amdgcn_rcp(lam);
+    r = r * (2.0 - lam * r);
+    r = r * (2.0 - lam * r);
+    return (T)((double)v * (r * norm));
+#endif
+}
+
 // Stage 3: amplitude / eigenvalue times the inverse transform's factor.
 // Grid: x over blockIdx.x, groups of four rows (j + n1 k, uniform per
 // block) strided over blockIdx.y, the four loads in flight together.
@@ -452,18 +471,7 @@ __global__ void k_grav_eigdiv(T *__restrict__ Y, const double *__restrict__ fx, 
             const int row = rb + u;
             if (row >= rows) break;
             const int k = row / n1, j = row - k * n1;
-            const double prod = f0 * fy[j] * fz[k];
-            const double lam = -6.0 * (1.0 - prod);
-#ifdef PPML_EXACT
-            Y[(long long)row * n0 + i] = (T)((double)v[u] / lam * norm);
-#else
-            // reciprocal by two Newton steps from the hardware estimate
-            // (within an ulp or two of the division)
-            double r = __builtin_amdgcn_rcp(lam);
-            r = r * (2.0 - lam * r);
-            r = r * (2.0 - lam * r);
-            Y[(long long)row * n0 + i] = (T)((double)v[u] * (r * norm));
-#endif
+            Y[(long long)row * n0 + i] = grav_amplitude<T>(v[u], f0 * fy[j], fz[k], norm);
         }
     }
 }
