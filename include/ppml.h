@@ -133,8 +133,8 @@ typedef struct {
  * eqs. (2)-(3) then use the central difference of the potential across each
  * cell, added to any fixed potential's gradient.  The scratch area grows by
  * the potential, a work array of the grid's size (two with an axis of more
- * than 512 cells in FP32, 256 in FP64), the shell terms of the outer layer of
- * cells and the sine tables (see ppml_scratch_bytes).  Grids with
+ * than 256 cells), the shell terms of the outer layer of cells and the sine
+ * tables (see ppml_scratch_bytes).  Grids with
  * self-gravity step alone, not in a batch. */
 
 /* Work-group tile shapes of the stage kernels for grids of ndim dimensions:

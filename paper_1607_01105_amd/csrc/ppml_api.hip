@@ -206,17 +206,18 @@ struct ScratchLayout {
 // Moment reduction of the self-gravity solve: fixed block count (fixed order).
 int grav_blocks(long long n) { return (int)std::min<long long>(1024, (n + 2047) / 2048 > 0 ? (n + 2047) / 2048 : 1); }
 
-// The kernels of ppml_sine.hpp hold a line's two halves in registers (in the
-// z pass its results too): up to SINE_TILES blocks of 16 a half, 512 cells in
-// FP32 and 256 in FP64, where the z pass fills the 512 registers of a lane.
-// A grid with a longer axis takes library products.
-template <typename T> constexpr int SINE_TILES = sizeof(T) == 4 ? 16 : 8;
+// The kernels of ppml_sine.hpp hold a line's two halves in registers, in the
+// z pass its results too: up to SINE_TILES blocks of 16 a half, axes of 256
+// cells.  A grid with a longer axis takes library products.  The solve,
+// library against kernels, in us: FP64 160^3 340 and 189, 192^3 478 and 370,
+// 240^3 739 and 694, 256^3 725 and 734; FP32 224^3 440 and 320; with kernels
+// built for longer lines FP32 272^3 822 and 975, 512x64x512 509 and 566.
+constexpr int SINE_TILES = 8;
 
 bool sine_kernels(const ppml_desc *d)
 {
-    const int most = 16 * (d->prec == PPML_FP64 ? SINE_TILES<double> : SINE_TILES<float>);
     for (int a = 0; a < 3; a++)
-        if (grav_no(d->n[a]) > most) return false;
+        if (grav_no(d->n[a]) > 16 * SINE_TILES) return false;
     return true;
 }
 
@@ -510,10 +511,6 @@ template <typename T, int KIND> int sine_pass(ppml_grid *g, const T *src, T *dst
     case 6: return sine_launch<T, 6, KIND>(g, src, dst, S, nl);
     case 7: return sine_launch<T, 7, KIND>(g, src, dst, S, nl);
     case 8: return sine_launch<T, 8, KIND>(g, src, dst, S, nl);
-    }
-    if constexpr (SINE_TILES<T> == 16) {
-        if (sine_tiles(n[axis]) == 12) return sine_launch<T, 12, KIND>(g, src, dst, S, nl);
-        return sine_launch<T, 16, KIND>(g, src, dst, S, nl);
     }
     return fail(PPML_EINVAL, "sine transform of %d cells", n[axis]);
 }

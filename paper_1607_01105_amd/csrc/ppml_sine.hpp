@@ -68,13 +68,8 @@ template <typename T> __host__ __device__ constexpr int sine_ld(int mt)
     return sizeof(T) == 4 ? 16 * mt + 4 : 16 * mt + 2;
 }
 
-// Blocks of 16 that a kernel for an axis of n cells works with: those of the
-// longer (odd) half up to 8; between 8 and 16 every fourth count is built.
-__host__ __device__ constexpr int sine_tiles(int n)
-{
-    const int t = (grav_no(n) + 15) / 16;
-    return t <= 8 ? t : t <= 12 ? 12 : 16;
-}
+// Blocks of 16 of the longer (odd) half of an axis of n cells.
+__host__ __device__ constexpr int sine_tiles(int n) { return (grav_no(n) + 15) / 16; }
 
 // Table of an axis: tiles of 16 rows of the odd half, then of the even half
 // (rows of sine_ld entries, zero beyond the half's extent), first with the
@@ -114,7 +109,7 @@ struct SineArgs {
 };
 
 // Launch shape: a block per CU, its LDS holding the whole table where that
-// fits (FP32: lines up to 256 cells, FP64: up to 160), else an even share of
+// fits (all but FP64 lines of more than 192 cells), else an even share of
 // it at a time; as many waves as their registers allow (a line's two halves
 // take MT / 2 times the element's bytes a lane, in the z pass the results as
 // much again, forward along x the shell terms).
@@ -152,7 +147,7 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
     constexpr int CT = SineShape<T, MT, KIND>::CT;
     constexpr int HALF = 16 * LD;
     constexpr int TILE16 = SineShape<T, MT, KIND>::TILE / 16;  // 16-byte words of a tile
-    constexpr int FULL = MT <= 8 ? MT - 1 : MT - 4;  // blocks of 16 that lie inside both halves
+    constexpr int FULL = MT - 1;  // blocks of 16 that lie inside both halves
     constexpr int QMAX = krow<T>(3, 0);
     extern __shared__ double sine_lds[];
     const T *P = (const T *)sine_lds;  // [CT][half][16][LD]
