@@ -209,9 +209,10 @@ int grav_blocks(long long n) { return (int)std::min<long long>(1024, (n + 2047) 
 // The kernels of ppml_sine.hpp hold a line's two halves in registers, in the
 // z pass its results too: up to SINE_TILES blocks of 16 a half, axes of 256
 // cells.  A grid with a longer axis takes library products.  The solve,
-// library against kernels, in us: FP64 160^3 340 and 189, 192^3 478 and 370,
-// 240^3 739 and 694, 256^3 725 and 734; FP32 224^3 440 and 320; with kernels
-// built for longer lines FP32 272^3 822 and 975, 512x64x512 509 and 566.
+// library against kernels, in us: FP64 160^3 338 and 182, 192^3 474 and 365,
+// 240^3 734 and 667, 256^3 719 and 700; FP32 160^3 215 and 129, 224^3 435 and
+// 293, 256^3 420 and 398; with kernels built for longer lines FP32 272^3 822
+// and 975, 512x64x512 509 and 566.
 constexpr int SINE_TILES = 8;
 
 bool sine_kernels(const ppml_desc *d)
@@ -543,11 +544,12 @@ template <typename T> int launch_gravity(ppml_grid *g)
     k_grav_moments_final<<<1, GRAV_THREADS, 0, g->stream>>>(g->gpart, nb, g->ctrl);
     const long long nshell = (long long)(n0 + 2) * (n1 + 2) * (n2 + 2) - N;
     k_grav_shell<T><<<(unsigned)((nshell + 255) / 256), 256, 0, g->stream>>>(gp, g->ctrl, g->d.grav_G, phi);
-    // shell terms of the outer layer, then the right-hand side's sums and
-    // differences into Y
+    // right-hand side of the outer layer or its shell terms alone, then the
+    // transforms or the right-hand side's sums and differences into Y
     T *E = (T *)g->gedge;
     const long long nedge = grav_edge_cells(n0, n1, n2);
-    k_grav_edge_terms<T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(phi, gp, E);
+    k_grav_edge_terms<T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(
+        phi, sine_kernels(&g->d) ? rho : (const T *)nullptr, g->grav_coef, gp, E);
     if (sine_kernels(&g->d)) {
         int rc;
         if ((rc = sine_pass<T, SINE_X_FWD>(g, rho, X))) return rc;

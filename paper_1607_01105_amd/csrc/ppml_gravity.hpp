@@ -32,7 +32,8 @@
 //      of the shell-padded potential, which the Eulerian kernel differences.
 // Tables (half-size sine matrices, eigenvalue factors) are built once by
 // k_grav_tables.  The kernels of ppml_sine.hpp take the place of steps 4 to 6
-// and of the sums and differences of step 3 on grids whose axes they cover.
+// and of the sums and differences of step 3 on grids whose axes they cover;
+// there k_grav_edge_terms forms the outer layer's whole right-hand side.
 #pragma once
 
 #include "ppml_device.hpp"
@@ -253,9 +254,11 @@ __global__ void k_grav_shell(GridParams gp, const Ctrl *__restrict__ ctrl, doubl
 // x ends of the other rows; a cell listed twice on a grid of extent 1 or 2
 // gets the same value twice): minus the stencil's weight times every shell
 // value the cell's stencil touches, in the stencil's (dz, dy, dx) order,
-// into E[s] for the cell's place s in that list.
+// into E[s] for the cell's place s in that list; with a density, the cell's
+// whole right-hand side (coef rho plus those terms) instead.
 template <typename T>
-__global__ void k_grav_edge_terms(const T *__restrict__ phi, GridParams gp, T *__restrict__ E)
+__global__ void k_grav_edge_terms(const T *__restrict__ phi, const T *__restrict__ rho, double coef, GridParams gp,
+                                  T *__restrict__ E)
 {
     const long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const int n0 = gp.n[0], n1 = gp.n[1], n2 = gp.n[2];
@@ -293,6 +296,7 @@ __global__ void k_grav_edge_terms(const T *__restrict__ phi, GridParams gp, T *_
                 const double w = nd == 1 ? 4.0 / 9.0 : (nd == 2 ? 1.0 / 9.0 : 1.0 / 36.0);
                 b = b - w * (double)phi[pad_index(gp, ii, jj, kk)];
             }
+    if (rho) b = b + coef * (double)rho[((long long)k * n1 + j) * n0 + i];
     E[s] = (T)b;
 }
 

@@ -26,8 +26,10 @@
 // matrix cores are busy for 63% of a y pass at 256^3 FP32).  A solve's passes
 // against two half-size library products an axis and direction with kernels
 // for the sums, the division and the differences between them (19 passes over
-// the grid): 150^3 FP64 140 us against 318, 256^3 FP32 367 against 375 (the
-// products alone 168 at the rate of a large FP32 product).  Blocks of four
+// the grid): 150^3 FP64 135 us against 318, 256^3 FP32 350 against 375 (the
+// products alone 168 at the rate of a large FP32 product).  The x forward pass
+// at 256^3 FP32 takes 63 us; with the shell terms added to every cell's
+// density as it was loaded (registers for 8 waves a block instead of 16) 85.  Blocks of four
 // waves with 64 KB of the table at a time took 79 us where a y pass at 256^3
 // takes 57.
 #pragma once
@@ -112,13 +114,13 @@ struct SineArgs {
 // fits (all but FP64 lines of more than 192 cells), else an even share of
 // it at a time; as many waves as their registers allow (a line's two halves
 // take MT / 2 times the element's bytes a lane, in the z pass the results as
-// much again, forward along x the shell terms).
+// much again).
 constexpr int SINE_LDS = 160 * 1024;
 template <typename T, int MT, int KIND> struct SineShape {
     static constexpr int TILE = 2 * 16 * sine_ld<T>(MT) * (int)sizeof(T);
     static constexpr int PARTS = (MT * TILE + SINE_LDS - 1) / SINE_LDS;
     static constexpr int CT = (MT + PARTS - 1) / PARTS;
-    static constexpr int REGS = 2 * MT * (int)sizeof(T) * (KIND == SINE_Z || KIND == SINE_X_FWD ? 2 : 1);
+    static constexpr int REGS = 2 * MT * (int)sizeof(T) * (KIND == SINE_Z ? 2 : 1);
     static constexpr int WAVES = REGS <= 64 ? 16 : REGS <= 160 ? 8 : 4;
 };
 
@@ -197,60 +199,48 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
         // the lines: cells b and n-1-b (forward) or odd and even modes
         // (inverse); zero beyond the half's extent
         T xo[4 * MT], xe[4 * MT];
-#pragma unroll
-        for (int p = 0; p < 4 * MT; p++) {
-            const int u = 16 * (p >> 2) + krow<T>(0, p & 3);  // row of group 0
-            if ((p >> 2) < FULL) {
-                xo[p] = at(src + u * st, in_up);
-                xe[p] = FWD ? at(src + (n - 1 - u - QMAX) * st, in_dn) : at(src + (no + u) * st, in_up);
-            } else {
-                const int b = u + qk;
-                const int bl = b < no ? b : no - 1, be = FWD ? n - 1 - bl : b < ne ? no + b : n - 1;
-                xo[p] = src[base + bl * st];
-                xe[p] = src[base + be * st];
-            }
-        }
+        double scale = 1.0, scale0 = 1.0;  // of the line's cells, of its two ends
         if constexpr (KIND == SINE_X_FWD) {
-            // shell terms: all cells of a line in the outer layer, the two
-            // ends of any other line
+            // a line in the outer layer comes whole from the right-hand side
+            // listed there, any other from the density but for its two ends
             const bool full = la == 0 || la == n1 - 1 || lb == 0 || lb == n2 - 1;
             const T *El = E + grav_edge_index(0, la, lb, n0, n1, n2);
-            int any = __builtin_amdgcn_readfirstlane(__any(full));
+            const T *up = (full ? El : src + base) + qk;
+            const T *dn = (full ? El : src + base) + (n - 1 - qk);
+            if (!full) scale = args.coef;
+            scale0 = q == 0 ? 1.0 : scale;
 #pragma unroll
-            for (int t = 0; t < MT; t++) {
-                // a branch of each block's own: the loads of one at a time
-                asm volatile("" : "+s"(any));
-                T el[4] = {T(0), T(0), T(0), T(0)}, eh[4] = {T(0), T(0), T(0), T(0)};
-                if (t == 0 || any) {
-#pragma unroll
-                    for (int s = 0; s < 4; s++) {
-                        const int b = 16 * t + krow<T>(0, s) + qk;
-                        if (full || b == 0) {
-                            const int bl = t < FULL || b < no ? b : no - 1;
-                            el[s] = El[bl];
-                            eh[s] = El[full ? n - 1 - bl : n > 1];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    const int p = 4 * t + s, b = 16 * t + krow<T>(0, s) + qk;
-                    // not formed before the block's turn: registers
-                    asm volatile("" : "+v"(xo[p]), "+v"(xe[p]));
-                    double lo = args.coef * (double)xo[p], hi = args.coef * (double)xe[p];
-                    lo = lo + (double)el[s];
-                    hi = hi + (double)eh[s];
-                    const bool pair = t < FULL || b < ne, in = t < FULL || b < no;
-                    xo[p] = in ? (T)(pair ? lo + hi : lo) : T(0);
-                    xe[p] = pair ? (T)(lo - hi) : T(0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            for (int p = 0; p < 4 * MT; p++) {
+                const int u = 16 * (p >> 2) + krow<T>(0, p & 3);
+                const int ul = (p >> 2) < FULL || u + qk < no ? u : no - 1 - qk;
+                xo[p] = up[ul];
+                xe[p] = dn[-ul];
             }
+            if (!full && q == 0) xo[0] = El[0], xe[0] = El[n > 1];
         } else {
 #pragma unroll
             for (int p = 0; p < 4 * MT; p++) {
-                const int b = 16 * (p >> 2) + krow<T>(0, p & 3) + qk;
-                const bool pair = (p >> 2) < FULL || b < ne, in = (p >> 2) < FULL || b < no;
+                const int u = 16 * (p >> 2) + krow<T>(0, p & 3);  // row of group 0
+                if ((p >> 2) < FULL) {
+                    xo[p] = at(src + u * st, in_up);
+                    xe[p] = FWD ? at(src + (n - 1 - u - QMAX) * st, in_dn) : at(src + (no + u) * st, in_up);
+                } else {
+                    const int b = u + qk;
+                    const int bl = b < no ? b : no - 1, be = FWD ? n - 1 - bl : b < ne ? no + b : n - 1;
+                    xo[p] = src[base + bl * st];
+                    xe[p] = src[base + be * st];
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < 4 * MT; p++) {
+            const int b = 16 * (p >> 2) + krow<T>(0, p & 3) + qk;
+            const bool pair = (p >> 2) < FULL || b < ne, in = (p >> 2) < FULL || b < no;
+            if constexpr (KIND == SINE_X_FWD) {
+                const double lo = (p ? scale : scale0) * (double)xo[p], hi = (p ? scale : scale0) * (double)xe[p];
+                xo[p] = in ? (T)(pair ? lo + hi : lo) : T(0);
+                xe[p] = pair ? (T)(lo - hi) : T(0);
+            } else {
                 const T lo = xo[p], hi = xe[p];
                 xo[p] = in ? (FWD && pair ? lo + hi : lo) : T(0);
                 xe[p] = pair ? (FWD ? lo - hi : hi) : T(0);
