@@ -6,7 +6,9 @@
 // host thread checks or converts about as fast.  Here threads take chunks of
 // the array in turn, each with two pinned buffers of its own: it checks, or
 // converts, one chunk while the other is on the bus, and FP32 states cross the
-// bus as FP32.
+// bus as FP32.  hipStreamPerThread names another stream in every thread, and
+// only the caller's is ordered with the caller's steps: on that handle the
+// caller's thread moves every chunk.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -142,6 +144,9 @@ struct XferDevice {
     }
 };
 
+// Most threads that may issue copies on the stream.
+inline int xfer_most(hipStream_t stream) { return stream == hipStreamPerThread ? 1 : XFER_THREADS; }
+
 inline int xfer_threads(size_t items, int most)
 {
     const unsigned hw = std::thread::hardware_concurrency();
@@ -217,7 +222,7 @@ hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src,
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};
     const XferDevice keep;
-    on_threads(xfer_threads(std::min<size_t>(items, 1 + (size_t)(there / XFER_LEAST)), XFER_THREADS), [&] {
+    on_threads(xfer_threads(std::min<size_t>(items, 1 + (size_t)(there / XFER_LEAST)), xfer_most(stream)), [&] {
         hipError_t e = hipSetDevice(device);
         XferLane *l = nullptr;
         if (e == hipSuccess) {
@@ -275,7 +280,7 @@ hipError_t xfer_download(int device, hipStream_t stream, const T *src, long long
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};
     const XferDevice keep;
-    on_threads(xfer_threads(items, XFER_THREADS), [&] {
+    on_threads(xfer_threads(items, xfer_most(stream)), [&] {
         hipError_t e = hipSetDevice(device);
         XferLane *l = nullptr;
         if (e == hipSuccess) {

@@ -1,0 +1,93 @@
+// CPU tests of ppml_transfer.hpp over the stand-in runtime: one per argument.
+#include "../../paper_1607_01105_amd/csrc/ppml_transfer.hpp"
+
+#include <cstdio>
+#include <string>
+
+using namespace ppml;
+
+static int failures = 0;
+#define CHECK(c)                                                         \
+    do {                                                                 \
+        if (!(c)) {                                                      \
+            failures++;                                                  \
+            std::printf("%s:%d: %s\n", __FILE__, __LINE__, #c);          \
+        }                                                                \
+    } while (0)
+
+static const hipStream_t OWN = (hipStream_t)0x1000;
+
+static std::vector<double> numbers(size_t n, double first)
+{
+    std::vector<double> v(n);
+    for (size_t i = 0; i < n; i++) v[i] = first + 0.5 * (double)(i % 4096);
+    return v;
+}
+
+// Three arrays, the second absent, to the "device" and back.
+template <typename T> static void round_trip(hipStream_t s, long long n, int device = 0)
+{
+    const std::vector<double> a = numbers((size_t)n, 1.0), b = numbers((size_t)n, 7.0);
+    const double *src[3] = {a.data(), nullptr, b.data()};
+    std::vector<T> dev((size_t)(3 * n), T(-1));
+    CHECK(xfer_upload<T>(device, s, src, 3, n, dev.data()) == hipSuccess);
+    hipStreamSynchronize(s);  // as the set calls do, for the zeros
+    bool same = true;
+    for (long long i = 0; i < n; i++)
+        same = same && dev[i] == (T)a[i] && dev[n + i] == T(0) && dev[2 * n + i] == (T)b[i];
+    CHECK(same);
+    std::vector<double> back((size_t)(3 * n), -1.0);
+    CHECK(xfer_download<T>(device, s, dev.data(), 3 * n, back.data()) == hipSuccess);
+    same = true;
+    for (long long i = 0; i < 3 * n; i++) same = same && back[i] == (double)dev[i];
+    CHECK(same);
+}
+
+static void sizes()
+{
+    for (long long n : {1ll, 65536ll, 65537ll, 262144ll, 700001ll}) {
+        round_trip<float>(OWN, n);
+        round_trip<double>(OWN, n);
+    }
+}
+
+static void several_calls()
+{
+    std::vector<std::thread> ts;
+    for (int t = 0; t < 4; t++)
+        ts.emplace_back([t] {
+            for (int i = 0; i < 3; i++) round_trip<float>((hipStream_t)(size_t)(0x1000 * (t + 1)), 300000 + t);
+        });
+    for (std::thread &t : ts) t.join();
+}
+
+// hipStreamPerThread is another stream in every thread: only the caller's is
+// ordered with the caller's work.
+static void per_thread_stream()
+{
+    round_trip<float>(hipStreamPerThread, 700001);
+    round_trip<double>(hipStreamPerThread, 700001);
+    // work that is still queued there comes before a read
+    const long long n = 700001;
+    std::vector<float> old((size_t)n, 1.0f), stepped((size_t)n, 2.0f);
+    std::vector<double> back((size_t)n);
+    hipMemcpyAsync(old.data(), stepped.data(), (size_t)n * sizeof(float), hipMemcpyHostToDevice, hipStreamPerThread);
+    CHECK(xfer_download<float>(0, hipStreamPerThread, old.data(), n, back.data()) == hipSuccess);
+    bool fresh = true;
+    for (double v : back) fresh = fresh && v == 2.0;
+    CHECK(fresh);
+    bool own = true;
+    for (std::thread::id id : stub().copied_by) own = own && id == std::this_thread::get_id();
+    CHECK(own);
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "sizes") sizes();
+    else if (what == "several_calls") several_calls();
+    else if (what == "per_thread_stream") per_thread_stream();
+    else return 2;
+    std::printf("%s: %d failure(s)\n", what.c_str(), failures);
+    return failures != 0;
+}
