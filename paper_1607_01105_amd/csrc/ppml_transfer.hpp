@@ -44,6 +44,7 @@ struct XferLane {
     void *buf[2] = {nullptr, nullptr};
     hipEvent_t ev[2] = {nullptr, nullptr};
     bool busy[2] = {false, false};
+    bool lost = false;  // a copy may still use a buffer: the lane is not used or freed again
 
     hipError_t init(int dev)
     {
@@ -61,6 +62,15 @@ struct XferLane {
             if (ev[i]) (void)hipEventDestroy(ev[i]);
             if (buf[i]) (void)hipHostFree(buf[i]);
         }
+    }
+    // After a copy of buffer i on the stream: its event, or where that cannot be
+    // recorded the copy's end.
+    hipError_t mark(int i, hipStream_t stream)
+    {
+        const hipError_t e = hipEventRecord(ev[i], stream);
+        busy[i] = e == hipSuccess;
+        if (e != hipSuccess && hipStreamSynchronize(stream) != hipSuccess) lost = true;
+        return e;
     }
     hipError_t wait(int i)
     {
@@ -95,6 +105,7 @@ public:
     }
     void give(XferLane *l)
     {
+        if (l->lost) return;
         {
             std::lock_guard<std::mutex> lock(mu_);
             if (idle_.size() < XFER_IDLE) {
@@ -253,8 +264,7 @@ hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src,
                 i += m;
             }
             e = hipMemcpyAsync(dst + beg, l->buf[b], (size_t)(end - beg) * sizeof(T), hipMemcpyHostToDevice, stream);
-            if (e == hipSuccess) e = hipEventRecord(l->ev[b], stream);
-            l->busy[b] = e == hipSuccess;
+            if (e == hipSuccess) e = l->mark(b, stream);
             b ^= 1;
         }
         if (l) {
@@ -296,8 +306,7 @@ hipError_t xfer_download(int device, hipStream_t stream, const T *src, long long
             if (err.load() != (int)hipSuccess || (at[b] = next.fetch_add(1)) >= items) return false;
             const long long beg = (long long)at[b] * C, m = std::min(n - beg, C);
             e = hipMemcpyAsync(l->buf[b], src + beg, (size_t)m * sizeof(T), hipMemcpyDeviceToHost, stream);
-            if (e == hipSuccess) e = hipEventRecord(l->ev[b], stream);
-            l->busy[b] = e == hipSuccess;
+            if (e == hipSuccess) e = l->mark(b, stream);
             return e == hipSuccess;
         };
         int b = 0;

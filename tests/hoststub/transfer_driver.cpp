@@ -81,12 +81,33 @@ static void per_thread_stream()
     CHECK(own);
 }
 
+// A copy whose event cannot be recorded has ended before its buffer goes back
+// to the pool, and the call reports the error.
+static void record_fails()
+{
+    const long long n = 700001;
+    const std::vector<double> a = numbers((size_t)n, 1.0);
+    const double *src[1] = {a.data()};
+    std::vector<float> dev((size_t)n);
+    std::vector<double> back((size_t)n);
+    for (int down = 0; down < 2; down++)
+        for (int k = 0; k < 3; k++) {
+            stub().fail_record = stub().records + k;
+            CHECK((down ? xfer_download<float>(0, OWN, dev.data(), n, back.data())
+                        : xfer_upload<float>(0, OWN, src, 1, n, dev.data())) != hipSuccess);
+            for (const auto &q : stub().queue) CHECK(q.second.empty());
+            stub().fail_record = -1;
+            round_trip<float>(OWN, n);
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "sizes") sizes();
     else if (what == "several_calls") several_calls();
     else if (what == "per_thread_stream") per_thread_stream();
+    else if (what == "record_fails") record_fails();
     else return 2;
     std::printf("%s: %d failure(s)\n", what.c_str(), failures);
     return failures != 0;
