@@ -164,18 +164,45 @@ inline int xfer_threads(size_t items, int most)
     return (int)std::min<size_t>(items, std::min<size_t>((size_t)most, hw > 0 ? hw : 1));
 }
 
-// The device's treatment of FP32 subnormals in conversions (the product build
-// flushes them to zero, the exact build keeps them), for the calling thread.
-class XferSubnormals {
+// Rounding of the host's checks and conversions, for the calling thread: to
+// nearest, no exception trapped and no flag left, whatever the caller (whose
+// settings its threads inherit) has set.  Conversions treat FP32 subnormals as
+// the device does: the product build flushes them to zero, the exact build
+// keeps them.
+class XferRounding {
 public:
-#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__) && !defined(PPML_EXACT)
-    XferSubnormals() : old_(_mm_getcsr()) { _mm_setcsr(old_ | 0x8040u); }  // flush results, read subnormals as zero
-    ~XferSubnormals() { _mm_setcsr(old_); }
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#ifdef PPML_EXACT
+    static constexpr unsigned FLUSH = 0;
+#else
+    static constexpr unsigned FLUSH = 0x8040;  // results to zero, subnormal operands read as zero
+#endif
+    explicit XferRounding(bool convert) : old_(_mm_getcsr()) { _mm_setcsr(0x1F80u | (convert ? FLUSH : 0u)); }
+    ~XferRounding() { _mm_setcsr(old_); }
 
 private:
     unsigned old_;
+#else
+    explicit XferRounding(bool) {}
 #endif
 };
+
+// Host FP64 values to the storage type, and back.
+template <typename T> void xfer_convert(const double *s, long long n, T *d)
+{
+    if (sizeof(T) == sizeof(double)) {
+        std::memcpy(d, s, (size_t)n * sizeof(T));
+        return;
+    }
+    const XferRounding mode(true);
+    for (long long i = 0; i < n; i++) d[i] = (T)s[i];
+}
+inline void xfer_widen(const double *s, long long n, double *d) { std::memcpy(d, s, (size_t)n * sizeof(double)); }
+inline void xfer_widen(const float *s, long long n, double *d)
+{
+    const XferRounding mode(true);
+    for (long long i = 0; i < n; i++) d[i] = (double)s[i];
+}
 
 // Whether every value is finite (and, where asked, positive).
 inline bool xfer_check(const double *a, long long n, bool positive)
@@ -188,6 +215,7 @@ inline bool xfer_check(const double *a, long long n, bool positive)
         for (size_t q; ok.load(std::memory_order_relaxed) && (q = next.fetch_add(1)) < items;) {
             const long long b = (long long)q * C, e = std::min(n, b + C);
             bool good = true;
+            const XferRounding mode(false);
             if (positive)
                 for (long long i = b; i < e; i++) good &= a[i] > 0.0 && a[i] <= 1.7976931348623157e308;
             else
@@ -251,15 +279,9 @@ hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src,
             const long long beg = beg_of[run] + (long long)(q - first[run]) * C, end = std::min(end_of[run], beg + C);
             if ((e = l->wait(b)) != hipSuccess) break;
             T *p = (T *)l->buf[b];
-            XferSubnormals mode;
             for (long long i = beg; i < end;) {
                 const long long f = i / n, lo = i - f * n, m = std::min(end - i, n - lo);
-                if (sizeof(T) == sizeof(double)) {
-                    std::memcpy(p, src[f] + lo, (size_t)m * sizeof(T));
-                } else {
-                    const double *s = src[f] + lo;
-                    for (long long j = 0; j < m; j++) p[j] = (T)s[j];
-                }
+                xfer_convert(src[f] + lo, m, p);
                 p += m;
                 i += m;
             }
@@ -300,7 +322,6 @@ hipError_t xfer_download(int device, hipStream_t stream, const T *src, long long
                 e = hipErrorOutOfMemory;
             }
         }
-        XferSubnormals mode;
         size_t at[2] = {0, 0};
         auto fetch = [&](int b) {
             if (err.load() != (int)hipSuccess || (at[b] = next.fetch_add(1)) >= items) return false;
@@ -319,10 +340,7 @@ hipError_t xfer_download(int device, hipStream_t stream, const T *src, long long
                 break;
             }
             const long long beg = (long long)at[b] * C, m = std::min(n - beg, C);
-            const T *p = (const T *)l->buf[b];
-            if (sizeof(T) == sizeof(double)) std::memcpy(dst + beg, p, (size_t)m * sizeof(T));
-            else
-                for (long long j = 0; j < m; j++) dst[beg + j] = (double)p[j];
+            xfer_widen((const T *)l->buf[b], m, dst + beg);
             b ^= 1;
             have = more;
         }

@@ -1,7 +1,9 @@
 // CPU tests of ppml_transfer.hpp over the stand-in runtime: one per argument.
 #include "../../paper_1607_01105_amd/csrc/ppml_transfer.hpp"
 
+#include <cfenv>
 #include <cstdio>
+#include <limits>
 #include <string>
 
 using namespace ppml;
@@ -101,6 +103,36 @@ static void record_fails()
         }
 }
 
+// The caller's floating-point environment reaches neither the conversions, which
+// round to nearest as the device does, nor is it changed by them.
+static void environment()
+{
+    std::vector<double> a(700001, 1.0 / 3.0);
+    const long long n = (long long)a.size();
+    const float nearest = (float)a[0];
+    const double *src[1] = {a.data()};
+    std::vector<float> dev(a.size());
+    for (int mode : {FE_UPWARD, FE_DOWNWARD, FE_TOWARDZERO, FE_TONEAREST}) {
+        std::feclearexcept(FE_ALL_EXCEPT);
+        std::fesetround(mode);
+        const hipError_t e = xfer_upload<float>(0, OWN, src, 1, n, dev.data());
+        const int after = std::fegetround(), raised = std::fetestexcept(FE_INEXACT);
+        std::fesetround(FE_TONEAREST);
+        CHECK(e == hipSuccess && after == mode && !raised);
+        bool same = true;
+        for (float v : dev) same = same && v == nearest;
+        CHECK(same);
+    }
+    a[n / 2] = std::numeric_limits<double>::quiet_NaN();
+    feenableexcept(FE_INEXACT | FE_INVALID);
+    CHECK(xfer_upload<float>(0, OWN, src, 1, n / 2, dev.data()) == hipSuccess);
+    const bool finite = xfer_check(a.data(), n, false), positive = xfer_check(a.data(), n, true);
+    fedisableexcept(FE_ALL_EXCEPT);
+    CHECK(!finite && !positive);
+    a[n / 2] = std::numeric_limits<double>::denorm_min();
+    CHECK(xfer_check(a.data(), n, true));
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -108,6 +140,7 @@ int main(int argc, char **argv)
     else if (what == "several_calls") several_calls();
     else if (what == "per_thread_stream") per_thread_stream();
     else if (what == "record_fails") record_fails();
+    else if (what == "environment") environment();
     else return 2;
     std::printf("%s: %d failure(s)\n", what.c_str(), failures);
     return failures != 0;
