@@ -48,12 +48,20 @@ struct XferLane {
 
     hipError_t init(int dev)
     {
-        device = dev;
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < 2 && e == hipSuccess; i++) e = hipHostMalloc(&buf[i], XFER_CHUNK, hipHostMallocPortable);
+        return e == hipSuccess ? bind(dev) : e;
+    }
+    // The events belong to a device (the current one), the buffers to all.
+    hipError_t bind(int dev)
+    {
         hipError_t e = hipSuccess;
         for (int i = 0; i < 2 && e == hipSuccess; i++) {
-            e = hipHostMalloc(&buf[i], XFER_CHUNK, hipHostMallocPortable);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming);
+            if (ev[i]) (void)hipEventDestroy(ev[i]);
+            ev[i] = nullptr;
+            e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming);
         }
+        device = e == hipSuccess ? dev : -1;
         return e;
     }
     void free()
@@ -81,23 +89,31 @@ struct XferLane {
 };
 
 // Lanes no call is using, shared by every grid of the process: a call takes
-// what it needs and gives it back; past XFER_IDLE they are freed.
+// what it needs, one of its device if there is one, and gives it back; past
+// XFER_IDLE they are freed.
 class XferPool {
 public:
     XferPool() { idle_.reserve(XFER_IDLE); }
+    // (device: the current one)
     XferLane *take(int device, hipError_t &err)
     {
+        XferLane *l = nullptr;
         {
             std::lock_guard<std::mutex> lock(mu_);
-            for (size_t i = 0; i < idle_.size(); i++)
-                if (idle_[i]->device == device) {
-                    XferLane *l = idle_[i];
-                    idle_.erase(idle_.begin() + (std::ptrdiff_t)i);
-                    return l;
-                }
+            size_t at = 0;
+            while (at < idle_.size() && idle_[at]->device != device) at++;
+            if (at == idle_.size()) at = 0;
+            if (at < idle_.size()) {
+                l = idle_[at];
+                idle_.erase(idle_.begin() + (std::ptrdiff_t)at);
+            }
         }
-        XferLane *l = new XferLane;
-        err = l->init(device);
+        if (l) {
+            err = l->device == device ? hipSuccess : l->bind(device);
+        } else {
+            l = new XferLane;
+            err = l->init(device);
+        }
         if (err == hipSuccess) return l;
         l->free();
         delete l;

@@ -133,6 +133,21 @@ static void environment()
     CHECK(xfer_check(a.data(), n, true));
 }
 
+// The buffers kept for one device serve another: no pinned memory is allocated
+// anew, and every event is recorded on its own device.
+static void devices()
+{
+    hipError_t e = hipSuccess;
+    std::vector<XferLane *> lanes;
+    for (size_t i = 0; i < XFER_IDLE; i++) lanes.push_back(xfer_pool().take(0, e));
+    for (XferLane *l : lanes) xfer_pool().give(l);
+    const int allocs = stub().host_allocs;
+    for (int i = 0; i < 3; i++)
+        for (int device = 0; device < 4; device++) round_trip<float>((hipStream_t)(size_t)(0x1000 + device), 700001, device);
+    CHECK(stub().host_allocs == allocs);
+    CHECK(stub().event_mismatches == 0);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -141,6 +156,7 @@ int main(int argc, char **argv)
     else if (what == "per_thread_stream") per_thread_stream();
     else if (what == "record_fails") record_fails();
     else if (what == "environment") environment();
+    else if (what == "devices") devices();
     else return 2;
     std::printf("%s: %d failure(s)\n", what.c_str(), failures);
     return failures != 0;
