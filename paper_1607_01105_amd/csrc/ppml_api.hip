@@ -748,15 +748,19 @@ template <typename T> void stage_slots(int device, int tile, int xf, long long &
 // 371^2 15.4, 15.6, 14.3, 20.9; 768x700 32.3, 27.2, 28.6, 31.8; 1500^2 97, 78,
 // 68, 65 (the tile kernels before: 13.9, 17.0, 31.2, 93); FP64 at 1, 2 rows:
 // 256^2 16.6, 15.3; 1500^2 189, 147 (18.7, 216).
-int sheet_rows(const std::vector<const GridParams *> &gps, int prec)
+// (grid(i): the i-th; allocates nothing, as the allocation-free entry point
+// comes through here)
+template <typename F> int sheet_rows(int count, int prec, F &&grid)
 {
     int best = 1;
     double best_t = 1e300;
     for (int r : SHEET_ROWS) {
         if (prec == PPML_FP64 && r > 2) break;
         double waves = 0.0;
-        for (const GridParams *gp : gps)
-            waves += (double)((gp->n[0] + SHEET_W - 1) / SHEET_W) * ((gp->n[1] + r - 1) / r);
+        for (int i = 0; i < count; i++) {
+            const GridParams &gp = grid(i);
+            waves += (double)((gp.n[0] + SHEET_W - 1) / SHEET_W) * ((gp.n[1] + r - 1) / r);
+        }
         const double t = (1.0 + r) * std::max(std::ceil(waves / 1024.0), 1.3);
         if (t < best_t) {
             best_t = t;
@@ -780,7 +784,7 @@ void set_rows(GridParams &gp, int rows)
 void set_tiling(GridParams &gp, int ndim, int prec, int v)
 {
     if (ndim == 2) {
-        set_rows(gp, sheet_rows({&gp}, prec));
+        set_rows(gp, sheet_rows(1, prec, [&](int) -> const GridParams & { return gp; }));
         return;
     }
     v = launch_tile(ndim, prec, v);
@@ -1567,9 +1571,8 @@ int batch_rebuild(ppml_batch *b)
         add(nd, 0);
         b->gn[nd] = n - b->goff[nd];
         if (nd == 2 && b->gn[2] > 0) {
-            std::vector<const GridParams *> gps;
-            for (int i = b->goff[2]; i < n; i++) gps.push_back(&b->h_ents[i].gp);
-            b->rows2 = sheet_rows(gps, b->prec);
+            const BatchEntry *ents = b->h_ents + b->goff[2];
+            b->rows2 = sheet_rows(b->gn[2], b->prec, [&](int i) -> const GridParams & { return ents[i].gp; });
             for (int i = b->goff[2]; i < n; i++) set_rows(b->h_ents[i].gp, b->rows2);
         }
         if (nd == 3 && b->gn[3] > 0) {
