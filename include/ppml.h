@@ -133,9 +133,10 @@ typedef struct {
  * eqs. (2)-(3) then use the central difference of the potential across each
  * cell, added to any fixed potential's gradient.  The scratch area grows by
  * the potential, a work array of the grid's size (two with an axis of more
- * than 256 cells), the shell terms of the outer layer of cells and the sine
- * tables (see ppml_scratch_bytes).  Grids with
- * self-gravity step alone, not in a batch. */
+ * than 256 cells), the right-hand side of the outer layer of cells and the
+ * sine tables (see ppml_scratch_bytes).  FP32 grids with an axis of at most 64
+ * cells hold these in FP64, between the stored density and the stored
+ * potential.  Grids with self-gravity step alone, not in a batch. */
 
 /* Work-group tile shapes of the stage kernels for grids of ndim dimensions:
  * ppml_tile_count returns how many there are (>= 1) or PPML_EINVAL;

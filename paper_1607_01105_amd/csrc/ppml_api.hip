@@ -222,12 +222,31 @@ bool sine_kernels(const ppml_desc *d)
     return true;
 }
 
+// Whether they run in FP64: for FP64 states, and for FP32 states of a grid with
+// an axis of at most SINE_SHORT cells.  In FP32 every pass rounds its sums of
+// mirror cells, where the library path forms and rounds them once for all axes;
+// on long axes the shorter sums of the products outweigh that, on short ones
+// they do not.  Error of the FP32 potential against 64 bits over the library
+// path's, max norm / rms, FP32 transforms: 6^3 1.40 / 1.22, 16^3 1.21 / 1.06, 32^3
+// 1.21 / 1.13, 48x48x200 1.30 / 1.19, 48^3 1.02 / 0.96, 70^3 0.94 / 0.95, 100^3
+// 0.97 / 0.96, 104^3 1.00 / 0.95, 128^3 0.78 / 0.80, 256^3 0.85 / 0.84; FP64
+// transforms: 6^3 0.35 / 0.26, 32^3 0.12 / 0.15, 64^3 0.08 / 0.10.  The solve in us,
+// library / FP32 / FP64 transforms: 24^3 88 / 45 / 46, 64^3 97 / 47 / 53, 48x200x48
+// 109 / 77 / 105, 64x256x256 209 / 143 / 187, 24x256x256 169 / 133 / 167.
+constexpr int SINE_SHORT = 64;
+
+bool sine_fp64(const ppml_desc *d)
+{
+    return d->prec == PPML_FP64 || d->n[0] <= SINE_SHORT || d->n[1] <= SINE_SHORT || d->n[2] <= SINE_SHORT;
+}
+
+size_t sine_elem(const ppml_desc *d) { return sine_kernels(d) && sine_fp64(d) ? sizeof(double) : elem(d); }
+
 size_t sine_table_bytes(const ppml_desc *d, int axis)
 {
     const int n = d->n[axis];
     if (!sine_kernels(d)) return (size_t)n * n * elem(d);
-    return d->prec == PPML_FP64 ? sine_table_count<double>(n) * sizeof(double)
-                                : sine_table_count<float>(n) * sizeof(float);
+    return sine_fp64(d) ? sine_table_count<double>(n) * sizeof(double) : sine_table_count<float>(n) * sizeof(float);
 }
 
 ScratchLayout layout(const ppml_desc *d)
@@ -248,7 +267,7 @@ ScratchLayout layout(const ppml_desc *d)
         L.phi = sz;
         sz += align_up((n0 + 2) * (n1 + 2) * (n2 + 2) * e);
         L.wx = sz;
-        sz += align_up(n0 * n1 * n2 * e);
+        sz += align_up(n0 * n1 * n2 * sine_elem(d));
         L.wy = sz;
         if (!sine_kernels(d)) sz += align_up(n0 * n1 * n2 * e);  // the passes of ppml_sine.hpp run in place
         L.sx = sz;
@@ -266,7 +285,7 @@ ScratchLayout layout(const ppml_desc *d)
         L.gpart = sz;
         sz += align_up((size_t)grav_blocks(ncells(d)) * GRAV_MOM * sizeof(double));
         L.gedge = sz;
-        sz += align_up((size_t)grav_edge_cells(d->n[0], d->n[1], d->n[2]) * e);
+        sz += align_up((size_t)grav_edge_cells(d->n[0], d->n[1], d->n[2]) * sine_elem(d));
     }
     L.total = sz;
     return L;
@@ -481,37 +500,38 @@ template <typename T> int sine_transform(ppml_grid *g, int axis, bool inverse, c
 
 constexpr int SINE_BLOCKS = 256;  // a block per CU
 
-template <typename T, int MT, int KIND>
-int sine_launch(ppml_grid *g, const T *src, T *dst, const T *S, int nlines)
+template <typename T, int MT, int KIND, typename ST>
+int sine_launch(ppml_grid *g, const SineIn<T, KIND, ST> *src, SineOut<T, KIND, ST> *dst, const T *S, int nlines)
 {
     using Shape = SineShape<T, MT, KIND>;
     constexpr int lds = Shape::CT * Shape::TILE;
     if (lds > 64 * 1024)
-        HIPCHK(hipFuncSetAttribute((const void *)k_sine<T, MT, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        HIPCHK(hipFuncSetAttribute((const void *)k_sine<T, MT, KIND, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     const int tiles = (nlines + 15) / 16;
     const int waves = std::max(1, std::min(Shape::WAVES, (tiles + SINE_BLOCKS - 1) / SINE_BLOCKS));
     const int blocks = std::min(SINE_BLOCKS, (tiles + waves - 1) / waves);
     const SineArgs args = {g->grav_coef, g->grav_norm};
-    k_sine<T, MT, KIND><<<blocks, 64 * waves, lds, g->stream>>>(src, dst, S, (const T *)g->gedge, g->fx, g->fy, g->fz,
-                                                                g->gp, args);
+    k_sine<T, MT, KIND, ST><<<blocks, 64 * waves, lds, g->stream>>>(src, dst, S, (const T *)g->gedge, g->fx, g->fy,
+                                                                    g->fz, g->gp, args);
     return PPML_OK;
 }
 
-template <typename T, int KIND> int sine_pass(ppml_grid *g, const T *src, T *dst)
+template <typename T, int KIND, typename ST>
+int sine_pass(ppml_grid *g, const SineIn<T, KIND, ST> *src, SineOut<T, KIND, ST> *dst)
 {
     constexpr int axis = KIND == SINE_Z ? 2 : KIND == SINE_Y_FWD || KIND == SINE_Y_INV ? 1 : 0;
     const int *n = g->gp.n;
     const T *S = (const T *)(axis == 0 ? g->sx : axis == 1 ? g->sy : g->sz);
     const int nl = axis == 0 ? n[1] * n[2] : axis == 1 ? n[0] * n[2] : n[0] * n[1];
     switch (sine_tiles(n[axis])) {
-    case 1: return sine_launch<T, 1, KIND>(g, src, dst, S, nl);
-    case 2: return sine_launch<T, 2, KIND>(g, src, dst, S, nl);
-    case 3: return sine_launch<T, 3, KIND>(g, src, dst, S, nl);
-    case 4: return sine_launch<T, 4, KIND>(g, src, dst, S, nl);
-    case 5: return sine_launch<T, 5, KIND>(g, src, dst, S, nl);
-    case 6: return sine_launch<T, 6, KIND>(g, src, dst, S, nl);
-    case 7: return sine_launch<T, 7, KIND>(g, src, dst, S, nl);
-    case 8: return sine_launch<T, 8, KIND>(g, src, dst, S, nl);
+    case 1: return sine_launch<T, 1, KIND, ST>(g, src, dst, S, nl);
+    case 2: return sine_launch<T, 2, KIND, ST>(g, src, dst, S, nl);
+    case 3: return sine_launch<T, 3, KIND, ST>(g, src, dst, S, nl);
+    case 4: return sine_launch<T, 4, KIND, ST>(g, src, dst, S, nl);
+    case 5: return sine_launch<T, 5, KIND, ST>(g, src, dst, S, nl);
+    case 6: return sine_launch<T, 6, KIND, ST>(g, src, dst, S, nl);
+    case 7: return sine_launch<T, 7, KIND, ST>(g, src, dst, S, nl);
+    case 8: return sine_launch<T, 8, KIND, ST>(g, src, dst, S, nl);
     }
     return fail(PPML_EINVAL, "sine transform of %d cells", n[axis]);
 }
@@ -525,6 +545,25 @@ template <typename T> void sine_tables(ppml_grid *g)
         const long long m = std::max<long long>(sine_table_count<T>(n), n);
         k_sine_table<T><<<(unsigned)((m + 255) / 256), 256, 0, g->stream>>>((T *)S[a], f[a], n);
     }
+}
+
+// The potential of a state stored as ST by transforms in T.
+template <typename T, typename ST> int sine_solve(ppml_grid *g)
+{
+    const GridParams &gp = g->gp;
+    const ST *rho = (const ST *)g->state;
+    ST *phi = (ST *)g->phi;
+    T *E = (T *)g->gedge, *X = (T *)g->wx;
+    const long long nedge = grav_edge_cells(gp.n[0], gp.n[1], gp.n[2]);
+    k_grav_edge_terms<ST, T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(phi, rho, g->grav_coef, gp, E);
+    int rc;
+    if ((rc = sine_pass<T, SINE_X_FWD, ST>(g, rho, X))) return rc;
+    if ((rc = sine_pass<T, SINE_Y_FWD, T>(g, X, X))) return rc;
+    if ((rc = sine_pass<T, SINE_Z, T>(g, X, X))) return rc;
+    if ((rc = sine_pass<T, SINE_Y_INV, T>(g, X, X))) return rc;
+    if ((rc = sine_pass<T, SINE_X_INV, ST>(g, X, phi))) return rc;
+    HIPCHK(hipGetLastError());
+    return PPML_OK;
 }
 
 // The self-gravity potential of the current state into g->phi (Sec. 2.5).
@@ -544,22 +583,12 @@ template <typename T> int launch_gravity(ppml_grid *g)
     k_grav_moments_final<<<1, GRAV_THREADS, 0, g->stream>>>(g->gpart, nb, g->ctrl);
     const long long nshell = (long long)(n0 + 2) * (n1 + 2) * (n2 + 2) - N;
     k_grav_shell<T><<<(unsigned)((nshell + 255) / 256), 256, 0, g->stream>>>(gp, g->ctrl, g->d.grav_G, phi);
-    // right-hand side of the outer layer or its shell terms alone, then the
-    // transforms or the right-hand side's sums and differences into Y
+    if (sine_kernels(&g->d)) return sine_fp64(&g->d) ? sine_solve<double, T>(g) : sine_solve<T, T>(g);
+    // shell terms of the outer layer, then the right-hand side's sums and
+    // differences into Y
     T *E = (T *)g->gedge;
     const long long nedge = grav_edge_cells(n0, n1, n2);
-    k_grav_edge_terms<T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(
-        phi, sine_kernels(&g->d) ? rho : (const T *)nullptr, g->grav_coef, gp, E);
-    if (sine_kernels(&g->d)) {
-        int rc;
-        if ((rc = sine_pass<T, SINE_X_FWD>(g, rho, X))) return rc;
-        if ((rc = sine_pass<T, SINE_Y_FWD>(g, X, X))) return rc;
-        if ((rc = sine_pass<T, SINE_Z>(g, X, X))) return rc;
-        if ((rc = sine_pass<T, SINE_Y_INV>(g, X, X))) return rc;
-        if ((rc = sine_pass<T, SINE_X_INV>(g, X, phi))) return rc;
-        HIPCHK(hipGetLastError());
-        return PPML_OK;
-    }
+    k_grav_edge_terms<T, T><<<(unsigned)((nedge + 255) / 256), 256, 0, g->stream>>>(phi, nullptr, 0.0, gp, E);
     const long long nrep = (long long)grav_no(n0) * grav_no(n1) * grav_no(n2);
     const unsigned nbr = (unsigned)((nrep + 255) / 256);
     k_grav_butterfly<T><<<nbr, 256, 0, g->stream>>>(rho, E, g->grav_coef, Y, gp);
@@ -1028,7 +1057,7 @@ int ppml_create(const ppml_desc *d, void *state_dev, void *scratch_dev, void *hi
         g->grav_coef = 4.0 * M_PI * d->grav_G * h * h;
         g->grav_norm = (2.0 / (double)(gp.n[0] + 1)) * (2.0 / (double)(gp.n[1] + 1)) * (2.0 / (double)(gp.n[2] + 1));
         if (sine_kernels(d)) {
-            if (d->prec == PPML_FP64) sine_tables<double>(g);
+            if (sine_fp64(d)) sine_tables<double>(g);
             else sine_tables<float>(g);
         } else {
             if (rocblas_create_handle(&g->blas) != rocblas_status_success) {

@@ -256,9 +256,9 @@ __global__ void k_grav_shell(GridParams gp, const Ctrl *__restrict__ ctrl, doubl
 // value the cell's stencil touches, in the stencil's (dz, dy, dx) order,
 // into E[s] for the cell's place s in that list; with a density, the cell's
 // whole right-hand side (coef rho plus those terms) instead.
-template <typename T>
+template <typename T, typename TE>
 __global__ void k_grav_edge_terms(const T *__restrict__ phi, const T *__restrict__ rho, double coef, GridParams gp,
-                                  T *__restrict__ E)
+                                  TE *__restrict__ E)
 {
     const long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const int n0 = gp.n[0], n1 = gp.n[1], n2 = gp.n[2];
@@ -297,7 +297,7 @@ __global__ void k_grav_edge_terms(const T *__restrict__ phi, const T *__restrict
                 b = b - w * (double)phi[pad_index(gp, ii, jj, kk)];
             }
     if (rho) b = b + coef * (double)rho[((long long)k * n1 + j) * n0 + i];
-    E[s] = (T)b;
+    E[s] = (TE)b;
 }
 
 // Place of cell (i, j, k) in the outer-layer list of k_grav_edge_terms (its

@@ -18,6 +18,10 @@
 // the first product as the right operand of the second: scaled by the
 // eigenvalue, they never leave the registers.
 //
+// The transforms of FP32 states run in FP64 where an axis is short (sine_fp64),
+// from the stored density to the stored potential: the work array and the outer
+// layer's list hold FP64 then.
+//
 // A line is read whole before any of it is written and no line belongs to
 // two waves, so y and z run in place.
 //
@@ -34,11 +38,14 @@
 // takes 57.
 #pragma once
 
+#include <type_traits>
+
 #include "ppml_gravity.hpp"
 
 namespace ppml {
 
-enum { SINE_X_FWD, SINE_Y_FWD, SINE_Z, SINE_Y_INV, SINE_X_INV };
+// (named: in kernel signatures an unnamed one has other names on host and device)
+enum SineKind : int { SINE_X_FWD, SINE_Y_FWD, SINE_Z, SINE_Y_INV, SINE_X_INV };
 
 typedef float sine_f4 __attribute__((ext_vector_type(4)));
 typedef double sine_d4 __attribute__((ext_vector_type(4)));
@@ -106,6 +113,10 @@ template <typename T> __global__ void k_sine_table(T *__restrict__ S, double *__
     S[t] = v;
 }
 
+// Element types of a pass's source and destination.
+template <typename T, int KIND, typename ST> using SineIn = std::conditional_t<KIND == SINE_X_FWD, ST, T>;
+template <typename T, int KIND, typename ST> using SineOut = std::conditional_t<KIND == SINE_X_INV, ST, T>;
+
 struct SineArgs {
     double coef, norm;  // right-hand side 4 pi G h^2, inverse transform's factor
 };
@@ -137,12 +148,16 @@ __device__ __forceinline__ sine_d4 sine_row(const double *row, int t, int q)
     return a;
 }
 
-template <typename T, int MT, int KIND>
+// (ST: storage type of the density and the potential, T that of the transforms)
+template <typename T, int MT, int KIND, typename ST>
 __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
-    const T *src, T *dst, const T *__restrict__ S, const T *__restrict__ E, const double *__restrict__ fx,
-    const double *__restrict__ fy, const double *__restrict__ fz, GridParams gp, SineArgs args)
+    const SineIn<T, KIND, ST> *src, SineOut<T, KIND, ST> *dst, const T *__restrict__ S, const T *__restrict__ E,
+    const double *__restrict__ fx, const double *__restrict__ fy, const double *__restrict__ fz, GridParams gp,
+    SineArgs args)
 {
     using V = typename SineVec<T>::type;
+    using In = SineIn<T, KIND, ST>;
+    using Out = SineOut<T, KIND, ST>;
     constexpr int LD = sine_ld<T>(MT);
     constexpr bool FWD = KIND <= SINE_Z, INV = KIND >= SINE_Z;
     constexpr int AXIS = KIND == SINE_Z ? 2 : KIND == SINE_Y_FWD || KIND == SINE_Y_INV ? 1 : 0;
@@ -190,11 +205,11 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
         const int out = KIND == SINE_X_INV ? (int)pad_index(gp, 0, la, lb) : base;
         // an element is a uniform pointer plus a lane's byte offset: that of
         // its group's first row (up), or of its last one counted backwards
-        auto at = [](const T *p, unsigned off) { return *(const T *)((const char *)p + off); };
-        auto put = [](T *p, unsigned off, T v) { *(T *)((char *)p + off) = v; };
-        const unsigned in_up = (unsigned)(base + qk * st) * (unsigned)sizeof(T);
-        const unsigned in_dn = (unsigned)(base + (QMAX - qk) * st) * (unsigned)sizeof(T);
-        const unsigned out_up = (unsigned)(out + qk * st) * (unsigned)sizeof(T);
+        auto at = [](const In *p, unsigned off) { return *(const In *)((const char *)p + off); };
+        auto put = [](Out *p, unsigned off, Out v) { *(Out *)((char *)p + off) = v; };
+        const unsigned in_up = (unsigned)(base + qk * st) * (unsigned)sizeof(In);
+        const unsigned in_dn = (unsigned)(base + (QMAX - qk) * st) * (unsigned)sizeof(In);
+        const unsigned out_up = (unsigned)(out + qk * st) * (unsigned)sizeof(Out);
 
         // the lines: cells b and n-1-b (forward) or odd and even modes
         // (inverse); zero beyond the half's extent
@@ -205,17 +220,21 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
             // listed there, any other from the density but for its two ends
             const bool full = la == 0 || la == n1 - 1 || lb == 0 || lb == n2 - 1;
             const T *El = E + grav_edge_index(0, la, lb, n0, n1, n2);
-            const T *up = (full ? El : src + base) + qk;
-            const T *dn = (full ? El : src + base) + (n - 1 - qk);
             if (!full) scale = args.coef;
             scale0 = q == 0 ? 1.0 : scale;
+            auto load = [&](const auto *line) {
+                const auto *up = line + qk, *dn = line + (n - 1 - qk);
 #pragma unroll
-            for (int p = 0; p < 4 * MT; p++) {
-                const int u = 16 * (p >> 2) + krow<T>(0, p & 3);
-                const int ul = (p >> 2) < FULL || u + qk < no ? u : no - 1 - qk;
-                xo[p] = up[ul];
-                xe[p] = dn[-ul];
-            }
+                for (int p = 0; p < 4 * MT; p++) {
+                    const int u = 16 * (p >> 2) + krow<T>(0, p & 3);
+                    const int ul = (p >> 2) < FULL || u + qk < no ? u : no - 1 - qk;
+                    xo[p] = up[ul];
+                    xe[p] = dn[-ul];
+                }
+            };
+            if constexpr (std::is_same_v<T, ST>) load(full ? El : src + base);
+            else if (full) load(El);
+            else load(src + base);
             if (!full && q == 0) xo[0] = El[0], xe[0] = El[n > 1];
         } else {
 #pragma unroll
@@ -259,8 +278,8 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
             for (int r = 0; r < 4; r++) {
                 const int u = 16 * t + krow<T>(0, r);
                 const int b = u + qk;
-                if (live && b < no) put(dst + u * st, out_up, so[r] + de[r]);
-                if (live && b < ne) dst[out + (n - 1 - b) * st] = so[r] - de[r];
+                if (live && b < no) put(dst + u * st, out_up, (Out)(so[r] + de[r]));
+                if (live && b < ne) dst[out + (n - 1 - b) * st] = (Out)(so[r] - de[r]);
             }
         };
         for (int t0 = 0; t0 < MT; t0 += CT) {
