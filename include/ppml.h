@@ -144,7 +144,8 @@ typedef struct {
  * of tx*ty threads owns a tx x ty column of cells; 3-D kernels march it
  * along z).  Used by the autotuner, which times the shapes on the caller's
  * workload; every shape computes bit-identical results.  In FP64 3-D
- * launches shape 0 stands for shape 2.  The kernels of 2-D
+ * launches shape 0 stands for shape 2 where that covers the grids with at most
+ * 1.1 times its cells.  The kernels of 2-D
  * grids and of short 1-D grids (up to 2304 cells in FP64, 3840 in FP32) have
  * no tiles: the shape changes nothing there. */
 int ppml_tile_count(int32_t ndim);

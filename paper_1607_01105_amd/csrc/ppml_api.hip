@@ -55,15 +55,31 @@ constexpr int NTILE[4] = {0, 3, 4, 4};
 constexpr int TILE_X[4][4] = {{0, 0, 0, 0}, {256, 128, 64, 0}, {32, 64, 16, 32}, {32, 64, 16, 32}};
 constexpr int TILE_Y[4][4] = {{0, 0, 0, 0}, {1, 1, 1, 0}, {8, 4, 16, 4}, {8, 4, 16, 4}};
 
-// Tile shape that index v stands for in launches.  FP64 3-D launches take 16x16
-// for the default: its Eulerian kernel fits a CU's LDS three times where 32x8
-// fits twice (us per step, 32x8 / 16x16: 512x512x64 2665 / 2340, 192^3 1177 /
-// 1084, 131x97x75 226 / 196, 64^3 75 / 72; 200x40x120 the other way, 195 / 203).
-int launch_tile(int ndim, int prec, int v) { return ndim == 3 && prec == PPML_FP64 && v == 0 ? 2 : v; }
+// Tile shape of the 3-D launches for the grids added: FP64 launches take 16x16
+// for the default, whose Eulerian kernel fits a CU's LDS three times where 32x8
+// fits twice, unless it takes more than TILE_FP64 times the cells to cover the
+// grids.  us per step at 32x8 / 16x16 (cells of 16x16 over those of 32x8):
+// 512x512x64 2648 / 2434 (1.00), 131x97x75 230 / 199 (0.97), 150^3 595 / 569
+// (1.05), 100x40x200 182 / 188 (1.05), 224x88x100 341 / 320 (1.09), 200x40x120
+// 204 / 206 and 200x40x40 87 / 102 (1.11), 512x72x64 432 / 409 (1.11), 160x56x100
+// 177 / 182 (1.14), 512x40x64 238 / 251 (1.20), 400x23x100 181 / 203 (1.28).
+constexpr double TILE_FP64 = 1.1;
+struct TileRule {
+    double cells[2] = {0.0, 0.0};  // of the tiles of 32x8, 16x16
+    void add(const GridParams &gp)
+    {
+        cells[0] += (double)((gp.n[0] + 31) / 32 * 32) * ((gp.n[1] + 7) / 8 * 8) * gp.n[2];
+        cells[1] += (double)((gp.n[0] + 15) / 16 * 16) * ((gp.n[1] + 15) / 16 * 16) * gp.n[2];
+    }
+    int tile(int prec, int v) const
+    {
+        return prec == PPML_FP64 && v == 0 && cells[1] <= TILE_FP64 * cells[0] ? 2 : v;
+    }
+};
 
 // Calls f(Tile<tx, ty>{}) for launch tile v of dimensionality NDIM (the tables
 // above, spelled out as template arguments).
-template <int NDIM, typename T, typename F> void with_tile(int v, F &&f)
+template <int NDIM, typename F> void with_tile(int v, F &&f)
 {
     if constexpr (NDIM == 1) {
         switch (v) {
@@ -76,10 +92,7 @@ template <int NDIM, typename T, typename F> void with_tile(int v, F &&f)
         case 1: f(Tile<64, 4>{}); break;
         case 2: f(Tile<16, 16>{}); break;
         case 3: f(Tile<32, 4>{}); break;
-        default:
-            if constexpr (NDIM == 3 && sizeof(T) == 8) f(Tile<16, 16>{});
-            else f(Tile<32, 8>{});
-            break;
+        default: f(Tile<32, 8>{}); break;
         }
     }
 }
@@ -299,6 +312,7 @@ struct ppml_grid {
     GridParams gpE, gpL;   // solo launches of the two stage kernels (own z chunks)
     GridParams gpB;        // solo launches of the row kernels of small 3-D grids
     bool brick;            // the grid takes those
+    int ltile;             // tile shape of the solo launches
     hipStream_t stream;
     int device;
     void *state;
@@ -375,7 +389,7 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
         k_lagr_brick<T><<<nb, SHEET_THREADS, 0, g->stream>>>(W, Us, gp, g->ctrl);
         if (ev) (void)hipEventRecord(ev[3], g->stream);
     } else {
-        with_tile<NDIM, T>(launch_tile(NDIM, g->d.prec, g->d.tile), [&](auto tl) {
+        with_tile<NDIM>(g->ltile, [&](auto tl) {
             using TL = decltype(tl);
             const GridParams &ge = g->gpE;
             const GridParams &gl = g->gpL;
@@ -749,11 +763,12 @@ int choose_chunks(long long tiles_xy, int nz, long long slots, double warm)
     return best;
 }
 
+// (tile: as launched)
 template <typename T> void stage_slots(int device, int tile, int xf, long long &slots_e, long long &slots_l)
 {
     int cus = 0, be = 0, bl = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
-    with_tile<3, T>(launch_tile(3, sizeof(T) == 8 ? PPML_FP64 : PPML_FP32, tile), [&](auto tl) {
+    with_tile<3>(tile, [&](auto tl) {
         using TL = decltype(tl);
         hipError_t e =
             xf == 2   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&be, k_euler<T, 3, TL::tx, TL::ty, 2>, TL::nt, 0)
@@ -810,13 +825,12 @@ void set_rows(GridParams &gp, int rows)
 // Work-group tiling of a grid for tile shape v: x/y tiles, and a z chunk
 // small enough that a 3-D grid alone gives the launch a few thousand work
 // groups (batches then fit the chunks of their 3-D grids together).
-void set_tiling(GridParams &gp, int ndim, int prec, int v)
+void set_tiling(GridParams &gp, int ndim, int prec, int v)  // v: as launched
 {
     if (ndim == 2) {
         set_rows(gp, sheet_rows(1, prec, [&](int) -> const GridParams & { return gp; }));
         return;
     }
-    v = launch_tile(ndim, prec, v);
     const int tx = TILE_X[ndim][v], ty = TILE_Y[ndim][v];
     gp.tiles[0] = (gp.n[0] + tx - 1) / tx;
     gp.tiles[1] = ndim >= 2 ? (gp.n[1] + ty - 1) / ty : 1;
@@ -935,7 +949,10 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
     gp.potential = d->potential;
     gp.first_order = (d->flags & PPML_FLAG_FIRST_ORDER) ? 1 : 0;
     for (int i = 0; i < 8; i++) gp.pot[i] = d->pot[i];
-    set_tiling(gp, d->ndim, d->prec, d->tile);
+    TileRule rule;
+    rule.add(gp);
+    g->ltile = d->ndim == 3 ? rule.tile(d->prec, d->tile) : d->tile;
+    set_tiling(gp, d->ndim, d->prec, g->ltile);
     // conserved ghost states of inflow faces, converted in FP64 as the state
     // is, into the control block
     double tab[6][6];
@@ -1010,8 +1027,8 @@ void init_chunks(ppml_grid *g)
     if (d->ndim == 3) {
         long long se, sl;
         const int xf = gp.potential == POT_HALO ? 2 : (gp.self_grav ? 1 : 0);
-        if (d->prec == PPML_FP64) stage_slots<double>(g->device, d->tile, xf, se, sl);
-        else stage_slots<float>(g->device, d->tile, xf, se, sl);
+        if (d->prec == PPML_FP64) stage_slots<double>(g->device, g->ltile, xf, se, sl);
+        else stage_slots<float>(g->device, g->ltile, xf, se, sl);
         const long long txy = (long long)gp.tiles[0] * gp.tiles[1];
         set_chunks(g->gpE, choose_chunks(txy, gp.n[2], se, 1.5));
         set_chunks(g->gpL, choose_chunks(txy, gp.n[2], sl, 3.0));
@@ -1541,7 +1558,7 @@ struct ppml_batch {
     int rows2;            // rows per wave of the 2-D launches
     int nline, nlds;      // 1-D grids stepped by the line kernel, first in the table; those of them in LDS
     long long line_nmax, lds_nmax;  // cells of the longest
-    int tile[4];          // tile shape of the launches per dimensionality
+    int tile[4], ltile[4];  // tile shape per dimensionality, as set and as launched
     bool dirty;
     long long version;
     hipGraph_t graph;
@@ -1565,7 +1582,12 @@ int batch_rebuild(ppml_batch *b)
     int n = 0;
     b->entry_slot.clear();
     bool beside = false;  // grids of more than one dimension share the batch
-    for (const ppml_grid *g : b->slots) beside = beside || (g && g->d.ndim > 1);
+    TileRule rule;
+    for (const ppml_grid *g : b->slots) {
+        beside = beside || (g && g->d.ndim > 1);
+        if (g && g->d.ndim == 3) rule.add(g->gp);
+    }
+    for (int nd = 1; nd <= 3; nd++) b->ltile[nd] = nd == 3 ? rule.tile(b->prec, b->tile[3]) : b->tile[nd];
     // kind: 0 stage kernels, 1 line kernel in LDS, 2 line kernel in memory
     auto kind_of = [&](const ppml_grid *g) {
         return line_grid(&g->d) ? 1 : (beside && g->d.ndim == 1 && g->d.n[0] <= LINE_BATCH_CELLS ? 2 : 0);
@@ -1576,7 +1598,7 @@ int batch_rebuild(ppml_batch *b)
             if (!g || g->d.ndim != nd || kind_of(g) != kind) continue;
             BatchEntry &e = b->h_ents[n];
             e.gp = g->gp;
-            set_tiling(e.gp, nd, b->prec, b->tile[nd]);
+            set_tiling(e.gp, nd, b->prec, b->ltile[nd]);
             e.state = g->state;
             e.half = g->half;
             e.ctrl = g->ctrl;
@@ -1611,8 +1633,8 @@ int batch_rebuild(ppml_batch *b)
             std::vector<GridParams *> gps;
             for (int i = b->goff[3]; i < n; i++) gps.push_back(&b->h_ents[i].gp);
             long long se, sl;
-            if (b->prec == PPML_FP64) stage_slots<double>(b->device, b->tile[3], 0, se, sl);
-            else stage_slots<float>(b->device, b->tile[3], 0, se, sl);
+            if (b->prec == PPML_FP64) stage_slots<double>(b->device, b->ltile[3], 0, se, sl);
+            else stage_slots<float>(b->device, b->ltile[3], 0, se, sl);
             const int cz = batch_cz3(gps, sl, 3.0);
             for (GridParams *gp : gps) set_chunks(*gp, (gp->n[2] + cz - 1) / cz);
         }
@@ -1648,7 +1670,7 @@ template <typename T, int NDIM> void batch_stage(ppml_batch *b, bool lagr, hipSt
             else k_euler_sheet_batch<T, R><<<b->gtiles[2], SHEET_THREADS, 0, st>>>(e, first, b->gn[2]);
         });
     } else {
-        with_tile<NDIM, T>(launch_tile(NDIM, b->prec, b->tile[NDIM]), [&](auto tl) {
+        with_tile<NDIM>(b->ltile[NDIM], [&](auto tl) {
             using TL = decltype(tl);
             const BatchEntry *e = b->d_ents + b->goff[NDIM];
             const int *first = b->d_first + b->goff[NDIM];
