@@ -96,6 +96,16 @@ def algorithmic_bytes_per_zone(kernel: str, ndim: int, width: int) -> int:
     return (2 * F - 1) * width if kernel == "euler" else 2 * F * width
 
 
+def tile_run(ndim: int, prec: str, tile: int):
+    """Tile shape of the launches: 2-D kernels have none, and for the FP64 3-D
+    default the library takes 32x8 or 16x16 by the grid."""
+    from paper_1607_01105_amd.ppml import ppml_tile_shape
+
+    if ndim == 2:
+        return None
+    return "default" if ndim == 3 and prec == "fp64" and tile == 0 else list(ppml_tile_shape(ndim, tile))
+
+
 def run_precision(prob, prec, steps, warmup, tile=0):
     import torch
 
@@ -174,7 +184,7 @@ def run_batched(seed=0, steps=200, tune=True):
             "plain_zone_updates_per_s": cells * steps / t_plain, "plain_s": t_plain,
             "batched_graph_zone_updates_per_s": cells * steps / t_batch, "batched_s": t_batch,
             "batched_first_call_s": t_first, "speedup": t_plain / t_batch, "bitwise_equal_to_plain": bool(same),
-            "tile_shapes": {str(nd): list(r["shape"]) for nd, r in tuned.items()}}
+            "tile_shapes": {str(nd): tile_run(nd, "fp32", r["tile"]) for nd, r in tuned.items()}}
 
 
 def run_served(n_requests=400, loads=(0.5, 0.8), seed=0, budget_gib=4.0, round_steps=50, capacity_requests=150):
@@ -341,7 +351,7 @@ def run_suite():
 
     from paper_1607_01105_amd import autotune
     from paper_1607_01105_amd import workloads as W
-    from paper_1607_01105_amd.ppml import Grid, ppml_tile_shape
+    from paper_1607_01105_amd.ppml import Grid
 
     out = {}
     for name, prob, precs in (("blast_waves_2400", W.blast_waves(), ("fp64",)),
@@ -357,7 +367,7 @@ def run_suite():
             t, _, n = g.run_to(prob.t_stop)
             sec = time.perf_counter() - t0
             out[name][prec] = {"steps": n, "t": t, "zone_updates_per_s": prob.cells * n / sec, "seconds": sec,
-                               "tile": list(ppml_tile_shape(prob.ndim, tile))}
+                               "tile": tile_run(prob.ndim, prec, tile)}
             if name.startswith("rayleigh_taylor"):
                 # growth of the seeded mode at the unstable interface over
                 # t = 3 .. 6 (untimed rerun), against linear theory sqrt(A g k)
@@ -401,7 +411,7 @@ def run_gravity(n=256, steps=50):
 
     from paper_1607_01105_amd import autotune
     from paper_1607_01105_amd import workloads as W
-    from paper_1607_01105_amd.ppml import Grid, ppml_tile_shape
+    from paper_1607_01105_amd.ppml import Grid
 
     prob = W.gravity_sphere(n, noise=0.01, seed=0)
     cells = prob.cells
@@ -429,7 +439,7 @@ def run_gravity(n=256, steps=50):
         mg, me, ml, k = g.get_timing_split()
         peak = 157.3 if prec == "fp32" else 78.6
         out[prec] = {"zone_updates_per_s": cells * steps / (ms * 1e-3), "ms_per_step": ms / steps,
-                     "tile": list(ppml_tile_shape(3, tile)),
+                     "tile": tile_run(3, prec, tile),
                      "split_ms": {"gravity": mg / k, "euler": me / k, "lagr": ml / k},
                      "transforms": {"algorithmic_gemm_flop": gemm_flop, "achieved_TFLOPs_over_gravity_solve":
                                     gemm_flop / (mg / k * 1e-3) / 1e12, "mfma_peak_TFLOPs": peak}}
@@ -465,7 +475,7 @@ def run_galaxy(steps=20, sizes=((256, ("fp32", "fp64")), (512, ("fp32",)))):
 
     from paper_1607_01105_amd import autotune
     from paper_1607_01105_amd import workloads as W
-    from paper_1607_01105_amd.ppml import Grid, ppml_tile_shape
+    from paper_1607_01105_amd.ppml import Grid
 
     out = {"workload": "isothermal self-gravitating disk (cs = 0.05, G = 1) in the paper's dark-matter halo "
                        "(density rho0 / (1 + (r/r0)^2) out to rh = 49.1 r0, r0 = 0.05), "
@@ -488,7 +498,7 @@ def run_galaxy(steps=20, sizes=((256, ("fp32", "fp64")), (512, ("fp32",)))):
             ms = t0.elapsed_time(t1)
             mg, me, ml, k = g.get_timing_split()
             out[str(n)][prec] = {"zone_updates_per_s": prob.cells * steps / (ms * 1e-3), "ms_per_step": ms / steps,
-                                 "tile": list(ppml_tile_shape(3, tile)),
+                                 "tile": tile_run(3, prec, tile),
                                  "split_ms": {"gravity": mg / k, "euler": me / k, "lagr": ml / k}}
             _log(f"[bench] galaxy {n}^3 {prec}: {ms / steps:.3f} ms/step (gravity {mg / k:.3f} ms)")
             del g
@@ -646,7 +656,9 @@ def main():
     achieved_gbs = bytes_launch / (ms_k * 1e-3) / 1e9
     from paper_1607_01105_amd.ppml import ppml_tile_shape
 
-    tx, ty = ppml_tile_shape(3, r["tuned"]["tile"] if r["tuned"] else 0)
+    tile = r["tuned"]["tile"] if r["tuned"] else 0
+    # (a cube's FP64 default is 16x16, shape 2)
+    tx, ty = ppml_tile_shape(3, 2 if head == "fp64" and tile == 0 else tile)
     key = f"k_{kern}<{'float' if width == 4 else 'double'},3,{tx},{ty}" + (
         f",{6 if width == 4 else 3}>" if kern == "lagr" else ">")
     traffic = measured_traffic(key)
@@ -673,9 +685,10 @@ def main():
         "dtype": "f32" if head == "fp32" else "f64",
         "data": "synthetic",
         "config": {"workload": WORKLOAD, "grid": [args.n] * 3, "gamma": 5.0 / 3.0, "cfl": 0.3, "seed": 0,
-                   "state": head, "tile": [tx, ty]},
-        "autotune": {p: {"ms_per_step_by_tile": {"x".join(map(str, ppml_tile_shape(3, v))): t
-                                                  for v, t in res[p]["tuned"]["ms_per_step"].items()}}
+                   "state": head, "tile": tile_run(3, head, r["tuned"]["tile"] if r["tuned"] else 0)},
+        "autotune": {p: {"ms_per_step_by_tile": {v if isinstance(v, str) else "x".join(map(str, v)): t
+                                                  for v, t in ((tile_run(3, p, i), t) for i, t in
+                                                               res[p]["tuned"]["ms_per_step"].items())}}
                      for p in res if res[p]["tuned"]},
         "kernels_ms": {"euler": r["ms_euler"], "lagr": r["ms_lagr"]},
         # the dominant kernel against the published vector peak of its type
@@ -705,7 +718,7 @@ def main():
         r64 = res["fp64"]
         out["fp64"] = {"value": cells * args.steps / (r64["ms"] * 1e-3), "ms_per_step": r64["ms"] / args.steps,
                        "kernels_ms": {"euler": r64["ms_euler"], "lagr": r64["ms_lagr"]},
-                       "tile": list(ppml_tile_shape(3, r64["tuned"]["tile"] if r64["tuned"] else 0))}
+                       "tile": tile_run(3, "fp64", r64["tuned"]["tile"] if r64["tuned"] else 0)}
     if not args.no_batch and "fp32" in res:
         print("[bench] batched configuration", file=sys.stderr, flush=True)
         out["batched"] = run_batched()
