@@ -193,7 +193,8 @@ int ppml_set_conserved(ppml_grid *g, const double *const *f, double rho_mean0, d
  * stream, launched on the grid's stream) unless per-step timing is on or
  * the grid has self-gravity; short 1-D grids take all steps of a call (1024 at
  * a time) in one kernel unless per-step timing is on; the results are the
- * same bits.
+ * same bits as long as the state stays physical (after a step that
+ * PPML_ENONFINITE reports, neither the state nor the time follows a rule).
  * Errors: PPML_EINVAL (nsteps < 0), PPML_ESTATE (state never set), PPML_EHIP. */
 int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop);
 

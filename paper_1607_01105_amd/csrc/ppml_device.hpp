@@ -555,8 +555,10 @@ __device__ __forceinline__ unsigned long long wave_umax(unsigned long long v)
 }
 
 // Maxima of |v| and c of the current state, folded from its slots (positive
-// FP64 values compare as their bits do; a NaN's bits exceed every number's, so
-// that it reaches the time step).  Every lane of the wave must be active.
+// FP64 values compare as their bits do).  Every lane of the wave must be active.
+// A NaN may be lost on the way here: the maxima over lanes and waves keep it or
+// not by where it lies.  Bad cells are reported by the error word alone, and what
+// the steps after one compute follows no rule.
 __device__ __forceinline__ void fold_max(Ctrl *c, int mslots, int set, unsigned long long &vm, unsigned long long &cm)
 {
     const int ln = threadIdx.x & 63;
