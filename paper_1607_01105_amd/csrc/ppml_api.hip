@@ -705,11 +705,11 @@ int finish_set(ppml_grid *g, double t, double rho_mean0)
 
 // The transfers of ppml_transfer.hpp; their threads and buffers may not be had.
 template <typename T>
-int upload(ppml_grid *g, const double *const *src, int nsrc, T *dst, const char *what)
+int upload(ppml_grid *g, const double *const *src, int nsrc, T *dst, XferHold &hold, const char *what)
 {
     hipError_t e;
     try {
-        e = xfer_upload<T>(g->device, g->stream, src, nsrc, g->gp.ncell, dst);
+        e = xfer_upload<T>(g->device, g->stream, src, nsrc, g->gp.ncell, dst, hold);
     } catch (const std::exception &) {
         return fail(PPML_ENOMEM, "%s: host allocation failed", what);
     }
@@ -1124,7 +1124,8 @@ int ppml_set_primitive(ppml_grid *g, const double *rho, const double *vx, const 
     double *prim = nullptr;
     HIPCHK(hipMallocAsync((void **)&prim, (size_t)5 * N * sizeof(double), g->stream));
     const double *src[5] = {rho, vx, vy, vz, p};
-    rc = upload<double>(g, src, 5, prim, "copy of the primitives");
+    XferHold hold;
+    rc = upload<double>(g, src, 5, prim, hold, "copy of the primitives");
     hipError_t e = hipSuccess;
     if (rc == PPML_OK) {
         int nb = (int)std::min<long long>(4096, (N + 255) / 256);
@@ -1159,8 +1160,9 @@ int ppml_set_conserved(ppml_grid *g, const double *const *f, double rho_mean0, d
         if (q >= 1 && q <= nd && src[q] && !all_finite(src[q], N, false))
             return fail(PPML_EINVAL, "field %d has non-finite values", fld);
     }
-    rc = g->d.prec == PPML_FP64 ? upload<double>(g, src, nfs, (double *)g->state, "set_conserved")
-                                : upload<float>(g, src, nfs, (float *)g->state, "set_conserved");
+    XferHold hold;
+    rc = g->d.prec == PPML_FP64 ? upload<double>(g, src, nfs, (double *)g->state, hold, "set_conserved")
+                                : upload<float>(g, src, nfs, (float *)g->state, hold, "set_conserved");
     if (rc) return rc;
     return finish_set(g, t, rho_mean0);
 }

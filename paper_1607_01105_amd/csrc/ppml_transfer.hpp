@@ -242,11 +242,38 @@ inline bool xfer_check(const double *a, long long n, bool positive)
     return ok.load();
 }
 
+// The lanes of an upload whose copies may still be under way: they go back to
+// the pool when the caller has waited for the stream, at the latest with this.
+class XferHold {
+public:
+    ~XferHold() { release(); }
+    void keep(XferLane *l) { lanes_[n_.fetch_add(1)] = l; }
+    hipError_t release()
+    {
+        hipError_t e = hipSuccess;
+        for (int i = n_.exchange(0) - 1; i >= 0; i--) {
+            for (int b = 0; b < 2; b++) {
+                const hipError_t w = lanes_[i]->wait(b);
+                if (e == hipSuccess) e = w;
+            }
+            xfer_pool().give(lanes_[i]);
+        }
+        return e;
+    }
+
+private:
+    XferLane *lanes_[XFER_THREADS];
+    std::atomic<int> n_{0};
+};
+
 // Host FP64 arrays src[0 .. nsrc), n values each (nullptr: zeros), to the device
-// array dst of nsrc n values of type T, on the stream.  The copies have left the
-// host arrays when the call returns.
+// array dst of nsrc n values of type T, on the stream.  The host arrays have been
+// read when the call returns; the copies end in the stream's order, and the
+// buffers they come from are held until then (waiting for them here cost a set
+// call of 64 cells 10 of its 75 us).
 template <typename T>
-hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src, int nsrc, long long n, T *dst)
+hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src, int nsrc, long long n, T *dst,
+                       XferHold &hold)
 {
     // chunks of the buffers' size, or smaller ones down to XFER_LEAST values
     // so that every thread has one to convert (256^2 FP32 primitives 0.34 ms
@@ -305,14 +332,7 @@ hipError_t xfer_upload(int device, hipStream_t stream, const double *const *src,
             if (e == hipSuccess) e = l->mark(b, stream);
             b ^= 1;
         }
-        if (l) {
-            // the buffers go back empty: a later call may use another stream
-            for (int i = 0; i < 2; i++) {
-                const hipError_t w = l->wait(i);
-                if (e == hipSuccess) e = w;
-            }
-            xfer_pool().give(l);
-        }
+        if (l) hold.keep(l);
         if (e != hipSuccess) err.store((int)e);
     });
     return (hipError_t)err.load();

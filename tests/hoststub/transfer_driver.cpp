@@ -32,8 +32,10 @@ template <typename T> static void round_trip(hipStream_t s, long long n, int dev
     const std::vector<double> a = numbers((size_t)n, 1.0), b = numbers((size_t)n, 7.0);
     const double *src[3] = {a.data(), nullptr, b.data()};
     std::vector<T> dev((size_t)(3 * n), T(-1));
-    CHECK(xfer_upload<T>(device, s, src, 3, n, dev.data()) == hipSuccess);
-    hipStreamSynchronize(s);  // as the set calls do, for the zeros
+    XferHold hold;
+    CHECK(xfer_upload<T>(device, s, src, 3, n, dev.data(), hold) == hipSuccess);
+    hipStreamSynchronize(s);  // as the set calls do
+    CHECK(hold.release() == hipSuccess);
     bool same = true;
     for (long long i = 0; i < n; i++)
         same = same && dev[i] == (T)a[i] && dev[n + i] == T(0) && dev[2 * n + i] == (T)b[i];
@@ -95,8 +97,11 @@ static void record_fails()
     for (int down = 0; down < 2; down++)
         for (int k = 0; k < 3; k++) {
             stub().fail_record = stub().records + k;
-            CHECK((down ? xfer_download<float>(0, OWN, dev.data(), n, back.data())
-                        : xfer_upload<float>(0, OWN, src, 1, n, dev.data())) != hipSuccess);
+            {
+                XferHold hold;
+                CHECK((down ? xfer_download<float>(0, OWN, dev.data(), n, back.data())
+                            : xfer_upload<float>(0, OWN, src, 1, n, dev.data(), hold)) != hipSuccess);
+            }
             for (const auto &q : stub().queue) CHECK(q.second.empty());
             stub().fail_record = -1;
             round_trip<float>(OWN, n);
@@ -115,17 +120,19 @@ static void environment()
     for (int mode : {FE_UPWARD, FE_DOWNWARD, FE_TOWARDZERO, FE_TONEAREST}) {
         std::feclearexcept(FE_ALL_EXCEPT);
         std::fesetround(mode);
-        const hipError_t e = xfer_upload<float>(0, OWN, src, 1, n, dev.data());
+        XferHold hold;
+        const hipError_t e = xfer_upload<float>(0, OWN, src, 1, n, dev.data(), hold);
         const int after = std::fegetround(), raised = std::fetestexcept(FE_INEXACT);
         std::fesetround(FE_TONEAREST);
-        CHECK(e == hipSuccess && after == mode && !raised);
+        CHECK(e == hipSuccess && after == mode && !raised && hold.release() == hipSuccess);
         bool same = true;
         for (float v : dev) same = same && v == nearest;
         CHECK(same);
     }
     a[n / 2] = std::numeric_limits<double>::quiet_NaN();
     feenableexcept(FE_INEXACT | FE_INVALID);
-    CHECK(xfer_upload<float>(0, OWN, src, 1, n / 2, dev.data()) == hipSuccess);
+    XferHold hold;
+    CHECK(xfer_upload<float>(0, OWN, src, 1, n / 2, dev.data(), hold) == hipSuccess);
     const bool finite = xfer_check(a.data(), n, false), positive = xfer_check(a.data(), n, true);
     fedisableexcept(FE_ALL_EXCEPT);
     CHECK(!finite && !positive);
@@ -148,6 +155,26 @@ static void devices()
     CHECK(stub().event_mismatches == 0);
 }
 
+// An upload does not wait for its copies, and no other call gets its buffers
+// while they are held.
+static void held()
+{
+    const long long n = 4096;
+    const std::vector<double> a = numbers((size_t)n, 1.0), b = numbers((size_t)n, 7.0);
+    const double *sa[1] = {a.data()}, *sb[1] = {b.data()};
+    std::vector<float> da((size_t)n), db((size_t)n);
+    {
+        XferHold ha, hb;
+        CHECK(xfer_upload<float>(0, OWN, sa, 1, n, da.data(), ha) == hipSuccess);
+        CHECK(!stub().queue[stub_runtime::key(OWN)].empty());
+        CHECK(xfer_upload<float>(0, OWN, sb, 1, n, db.data(), hb) == hipSuccess);
+    }
+    CHECK(stub().queue[stub_runtime::key(OWN)].empty());
+    bool same = true;
+    for (long long i = 0; i < n; i++) same = same && da[i] == (float)a[i] && db[i] == (float)b[i];
+    CHECK(same);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -157,6 +184,7 @@ int main(int argc, char **argv)
     else if (what == "record_fails") record_fails();
     else if (what == "environment") environment();
     else if (what == "devices") devices();
+    else if (what == "held") held();
     else return 2;
     std::printf("%s: %d failure(s)\n", what.c_str(), failures);
     return failures != 0;

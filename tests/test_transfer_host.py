@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 STUB = os.path.join(ROOT, "tests", "hoststub")
 BUILDS = {"plain": [], "thread": ["-fsanitize=thread"],
           "address": ["-fsanitize=address,undefined", "-fno-sanitize-recover=all"]}
-CASES = ["sizes", "several_calls", "per_thread_stream", "record_fails", "environment", "devices"]
+CASES = ["sizes", "several_calls", "per_thread_stream", "record_fails", "environment", "devices", "held"]
 
 
 @pytest.fixture(scope="module", params=list(BUILDS))
