@@ -146,8 +146,8 @@ typedef struct {
  * workload; every shape computes bit-identical results.  In FP64 3-D
  * launches shape 0 stands for shape 2 where that covers the grids with at most
  * 1.1 times its cells.  The kernels of 2-D
- * grids and of short 1-D grids (up to 2304 cells in FP64, 3840 in FP32) have
- * no tiles: the shape changes nothing there. */
+ * grids and of short 1-D grids (up to 2304 cells in FP64, 3840 in FP32; fewer
+ * in calls of one to three steps) have no tiles: the shape changes nothing there. */
 int ppml_tile_count(int32_t ndim);
 int ppml_tile_shape(int32_t ndim, int32_t variant, int32_t *tx, int32_t *ty);
 

@@ -419,10 +419,23 @@ template <typename T, int NDIM> void launch_stages(ppml_grid *g, hipEvent_t *ev)
 // 11.7, 1024 5.4 / 12.2, 2048 9.8 / 12.4, 2500 12.4 / 12.5; FP32 64 1.4 / 8.1,
 // 512 2.3 / 9.4, 2048 5.8 / 10.3, 3500 9.5 / 10.6, 4096 11.3 / 10.7.
 template <typename T> constexpr long long line_cells() { return sizeof(T) == 8 ? 2304 : 3840; }
-
-bool line_grid(const ppml_desc *d)
+// A call's steps share one filling and emptying of the LDS, so calls of one to
+// three steps take the kernel for shorter grids only: us per step, FP64 calls of
+// 1 step 1800 cells 14.1 / 14.8, 2150 16.0 / 14.8, of 2 2150 13.2 / 13.8, 2304 14.6 /
+// 14.1; FP32 of 1 2700 12.6 / 13.1, 3000 13.5 / 12.8, of 2 3300 11.7 / 12.2, 3600
+// 12.7 / 12.2, of 3 3600 11.7 / 11.9, 3840 12.0 / 11.7.
+template <typename T> constexpr long long line_cells(long long nsteps)
 {
-    return d->ndim == 1 && d->n[0] <= (d->prec == PPML_FP64 ? line_cells<double>() : line_cells<float>());
+    if (nsteps == 1) return sizeof(T) == 8 ? 1856 : 2752;
+    if (nsteps == 2) return sizeof(T) == 8 ? 2176 : 3392;
+    if (nsteps == 3) return sizeof(T) == 8 ? 2304 : 3712;
+    return line_cells<T>();
+}
+
+// (nsteps: of the call; 0: of calls of any length)
+bool line_grid(const ppml_desc *d, long long nsteps = 0)
+{
+    return d->ndim == 1 && d->n[0] <= (d->prec == PPML_FP64 ? line_cells<double>(nsteps) : line_cells<float>(nsteps));
 }
 
 // Beside the launches of 2-D or 3-D grids the line kernel also takes longer
@@ -1236,7 +1249,7 @@ int ppml_step(ppml_grid *g, int32_t nsteps, double dt_fixed, double t_stop)
     if (g->in_batch) return fail(PPML_ESTATE, "grid is stepped by its batch");
     // per-step timing splits the step into its stage kernels
     const bool timing = (size_t)(4 * (g->timed + 1)) <= g->ev.size();
-    const bool line = line_grid(&g->d);
+    const bool line = line_grid(&g->d, nsteps);
     if (line && !timing)
         return g->d.prec == PPML_FP64 ? launch_line<double>(g, nsteps, dt_fixed, t_stop, true)
                                       : launch_line<float>(g, nsteps, dt_fixed, t_stop, true);
@@ -1327,7 +1340,7 @@ int ppml_step_noalloc(const ppml_desc *d, void *state_dev, double rho_mean0, dou
     // control block and the maxima slots by the reset, the mean density and the
     // partials by the kernels below, the stage output by the Eulerian kernel
     if ((rc = finish_set_async(&g, t0, rho_mean0))) return rc;
-    if (nsteps > 0 && line_grid(d)) {
+    if (nsteps > 0 && line_grid(d, nsteps)) {
         rc = d->prec == PPML_FP64 ? launch_line<double>(&g, nsteps, dt_fixed, t_stop, true)
                                   : launch_line<float>(&g, nsteps, dt_fixed, t_stop, true);
         if (rc) return rc;
@@ -1558,6 +1571,8 @@ struct ppml_batch {
     std::vector<int> entry_slot;
     int goff[4], gn[4], gtiles[4];  // grids stepped by the stage kernels, per dimensionality
     int rows2;            // rows per wave of the 2-D launches
+    int few;              // steps of the calls the table is built for, 0: four and more
+    bool few_matters;     // some grid takes the line kernel by the steps of a call
     int nline, nlds;      // 1-D grids stepped by the line kernel, first in the table; those of them in LDS
     long long line_nmax, lds_nmax;  // cells of the longest
     int tile[4], ltile[4];  // tile shape per dimensionality, as set and as launched
@@ -1570,7 +1585,7 @@ struct ppml_batch {
     // grids of different dimensionalities share nothing: their launch chains
     // run as parallel branches (streams forked from and joined to the batch
     // stream, default priority), so the 1-D launches overlap the 2-D and 3-D
-    // ones instead of adding their time; side[0] runs the line kernel
+    // ones instead of adding their time; side[0] runs the line kernel.
     hipStream_t side[4];
     hipEvent_t ev_fork, ev_join[4];
 };
@@ -1585,14 +1600,18 @@ int batch_rebuild(ppml_batch *b)
     b->entry_slot.clear();
     bool beside = false;  // grids of more than one dimension share the batch
     TileRule rule;
+    bool near = false;  // 1-D grids near the line kernel's limit
     for (const ppml_grid *g : b->slots) {
+        near = near || (g && line_grid(&g->d) && !line_grid(&g->d, 1));
         beside = beside || (g && g->d.ndim > 1);
         if (g && g->d.ndim == 3) rule.add(g->gp);
     }
     for (int nd = 1; nd <= 3; nd++) b->ltile[nd] = nd == 3 ? rule.tile(b->prec, b->tile[3]) : b->tile[nd];
+    b->few_matters = near && !beside;
     // kind: 0 stage kernels, 1 line kernel in LDS, 2 line kernel in memory
     auto kind_of = [&](const ppml_grid *g) {
-        return line_grid(&g->d) ? 1 : (beside && g->d.ndim == 1 && g->d.n[0] <= LINE_BATCH_CELLS ? 2 : 0);
+        if (line_grid(&g->d, beside ? 0 : b->few)) return 1;
+        return beside && g->d.ndim == 1 && g->d.n[0] <= LINE_BATCH_CELLS ? 2 : 0;
     };
     auto add = [&](int nd, int kind) {
         for (int s = 0; s < b->capacity; s++) {
@@ -1766,6 +1785,8 @@ int ppml_batch_create(int32_t capacity, size_t budget_bytes, void *hip_stream, p
     b->h_steps = nullptr;
     b->dirty = true;
     b->nline = b->nlds = 0;
+    b->few = 0;
+    b->few_matters = false;
     b->line_nmax = b->lds_nmax = 0;
     b->rows2 = 1;
     b->d_first = nullptr;
@@ -1861,7 +1882,10 @@ int ppml_batch_step(ppml_batch *b, int32_t nsteps, const int32_t *steps_per_slot
     if (nsteps < 0) return fail(PPML_EINVAL, "nsteps must be >= 0");
     if (!std::isfinite(dt_fixed) || !std::isfinite(t_stop)) return fail(PPML_EINVAL, "dt_fixed and t_stop must be finite");
     HIPCHK(hipStreamSynchronize(b->stream));  // staging buffers are free again
+    const int few = nsteps > 0 && nsteps < 4 ? nsteps : 0;
+    if (b->few_matters && nsteps > 0 && few != b->few) b->dirty = true;
     if (b->dirty) {
+        b->few = few;
         int rc = batch_rebuild(b);
         if (rc) return rc;
     }
