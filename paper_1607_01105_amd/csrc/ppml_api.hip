@@ -1015,10 +1015,17 @@ int init_grid(ppml_grid *g, const ppml_desc *d, void *state_dev, void *scratch_d
 // 58x27x148 (3996) 54 / 39, 64^3 (8192) 48 / 62, 100^3 (20000) 105 / 115; FP64
 // 24^3 42 / 30, 40x60x30 56 / 45, 58x27x148 88 / 68, 64^3 71 / 114.
 constexpr long long BRICK_WAVES = 4096;
+// FP64 rows of up to eight cells (a launch of such strips takes 5 us longer than
+// of wider ones, in both precisions) win over the march from some hundred on: us
+// per step, march / rows: 5^3 33.2 / 36.6, 8^3 34.5 / 37.8, 8x16x16 35.1 / 36.8,
+// 6x12x30 36.6 / 36.0, 4x32x32 42.7 / 34.7; 9^3 34.5 / 28.2.
+constexpr long long BRICK_NARROW = 8, BRICK_NARROW_WAVES = 512;
 bool brick_grid(const ppml_desc *d, const GridParams &gp)
 {
-    return d->ndim == 3 && d->tile == 0 && !gp.any_inflow &&
-           (d->n[0] + SHEET_W - 1) / SHEET_W * d->n[1] * d->n[2] <= BRICK_WAVES;
+    const long long waves = (d->n[0] + SHEET_W - 1) / SHEET_W * d->n[1] * d->n[2];
+    if (d->ndim != 3 || d->tile != 0 || gp.any_inflow) return false;
+    if (d->prec == PPML_FP64 && d->n[0] <= BRICK_NARROW && waves < BRICK_NARROW_WAVES) return false;
+    return waves <= BRICK_WAVES;
 }
 
 // Z chunks of the solo stage launches, fitted to the resident work groups of
