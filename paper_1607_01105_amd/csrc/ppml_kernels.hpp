@@ -8,7 +8,7 @@
 //   k_lagr  : Lagrangian stage (Sec. 2.3): 9-point transverse velocity,
 //             density-weighted interface velocity, upwind parabolic fluxes
 //             of all conserved densities, unsplit update; then the
-//             total-energy correction (Sec. 2.4) and the per-wave maxima of
+//             total-energy correction (Sec. 2.4) and the work groups' maxima of
 //             |v| and c for the next CFL step (Sec. 2.1).  U^{n+1/2} -> U^{n+1}.
 //
 // Work decomposition (3-D): a workgroup owns a TX x TY column tile in (x, y)
