@@ -652,14 +652,12 @@ template <typename T> int launch_step(ppml_grid *g, hipEvent_t *ev)
     return PPML_OK;
 }
 
-template <typename T> void launch_totals(ppml_grid *g, double mean_cells)
+// Totals of the state; partial: 48 bytes for each of totals_blocks.
+template <typename T> void launch_totals(ppml_grid *g, double mean_cells, double *partial)
 {
     const long long N = g->gp.ncell;
     int nb = totals_blocks(N);
     long long chunk = (N + nb - 1) / nb;
-    // the partial sums go to the stage output's area (48 bytes per 4096 cells,
-    // at least 256 bytes), which holds nothing between steps
-    double *partial = (double *)g->half;
     k_totals_partial<T><<<nb, TOT_THREADS, 0, g->stream>>>((const T *)g->state, N, nfields(&g->d), chunk, partial);
     k_totals_final<<<1, TOT_THREADS, 0, g->stream>>>(partial, nb, nfields(&g->d), g->d.ndim, g->totals, g->ctrl,
                                                       mean_cells);
@@ -696,11 +694,14 @@ int finish_set_async(ppml_grid *g, double t, double rho_mean0)
 {
     k_ctrl_reset<<<1, 2 * MSLOT_MAX, 0, g->stream>>>(g->ctrl, g->gp.mslots, t, rho_mean0);
     HIPCHK(hipGetLastError());
+    // the partial sums go to the stage output's area (at least 256 bytes), which
+    // holds nothing as long as the state is being set
+    double *const partial = (double *)g->half;
     if (g->d.prec == PPML_FP64) {
-        launch_totals<double>(g, rho_mean0 > 0.0 ? 0.0 : (double)g->gp.ncell);
+        launch_totals<double>(g, rho_mean0 > 0.0 ? 0.0 : (double)g->gp.ncell, partial);
         launch_speeds<double>(g);
     } else {
-        launch_totals<float>(g, rho_mean0 > 0.0 ? 0.0 : (double)g->gp.ncell);
+        launch_totals<float>(g, rho_mean0 > 0.0 ? 0.0 : (double)g->gp.ncell, partial);
         launch_speeds<float>(g);
     }
     HIPCHK(hipGetLastError());
@@ -1435,9 +1436,15 @@ int ppml_totals(ppml_grid *g, double out[6])
     if ((rc = settle(g))) return rc;
     if (!out) return fail(PPML_EINVAL, "out is NULL");
     if (!g->has_state) return fail(PPML_ESTATE, "state was never set");
-    if (g->d.prec == PPML_FP64) launch_totals<double>(g, 0.0);
-    else launch_totals<float>(g, 0.0);
-    HIPCHK(hipGetLastError());
+    // (a buffer of its own: a read leaves the stage output alone, which another
+    // thread's batch call may be using)
+    double *partial = nullptr;
+    HIPCHK(hipMallocAsync((void **)&partial, (size_t)totals_blocks(g->gp.ncell) * 6 * sizeof(double), g->stream));
+    if (g->d.prec == PPML_FP64) launch_totals<double>(g, 0.0, partial);
+    else launch_totals<float>(g, 0.0, partial);
+    const hipError_t e = hipGetLastError();
+    (void)hipFreeAsync(partial, g->stream);
+    HIPCHK(e);
     HIPCHK(hipMemcpyAsync(out, g->totals, 6 * sizeof(double), hipMemcpyDeviceToHost, g->stream));
     HIPCHK(hipStreamSynchronize(g->stream));
     return PPML_OK;
