@@ -220,10 +220,11 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
             // listed there, any other from the density but for its two ends
             const bool full = la == 0 || la == n1 - 1 || lb == 0 || lb == n2 - 1;
             const T *El = E + grav_edge_index(0, la, lb, n0, n1, n2);
-            if (!full) scale = args.coef;
-            scale0 = q == 0 ? 1.0 : scale;
-            auto load = [&](const auto *line) {
-                const auto *up = line + qk, *dn = line + (n - 1 - qk);
+            if constexpr (std::is_same_v<T, ST>) {
+                const T *up = (full ? El : src + base) + qk;
+                const T *dn = (full ? El : src + base) + (n - 1 - qk);
+                if (!full) scale = args.coef;
+                scale0 = q == 0 ? 1.0 : scale;
 #pragma unroll
                 for (int p = 0; p < 4 * MT; p++) {
                     const int u = 16 * (p >> 2) + krow<T>(0, p & 3);
@@ -231,10 +232,23 @@ __global__ __launch_bounds__((64 * SineShape<T, MT, KIND>::WAVES)) void k_sine(
                     xo[p] = up[ul];
                     xe[p] = dn[-ul];
                 }
-            };
-            if constexpr (std::is_same_v<T, ST>) load(full ? El : src + base);
-            else if (full) load(El);
-            else load(src + base);
+            } else {
+                // (a lambda above as well cost the pass 3 of 63 us at 256^3)
+                auto load = [&](const auto *line) {
+                    const auto *up = line + qk, *dn = line + (n - 1 - qk);
+#pragma unroll
+                    for (int p = 0; p < 4 * MT; p++) {
+                        const int u = 16 * (p >> 2) + krow<T>(0, p & 3);
+                        const int ul = (p >> 2) < FULL || u + qk < no ? u : no - 1 - qk;
+                        xo[p] = up[ul];
+                        xe[p] = dn[-ul];
+                    }
+                };
+                if (!full) scale = args.coef;
+                scale0 = q == 0 ? 1.0 : scale;
+                if (full) load(El);
+                else load(src + base);
+            }
             if (!full && q == 0) xo[0] = El[0], xe[0] = El[n > 1];
         } else {
 #pragma unroll

@@ -246,7 +246,7 @@ inline bool xfer_check(const double *a, long long n, bool positive)
 // the pool when the caller has waited for the stream, at the latest with this.
 class XferHold {
 public:
-    ~XferHold() { release(); }
+    ~XferHold() { (void)release(); }
     void keep(XferLane *l) { lanes_[n_.fetch_add(1)] = l; }
     hipError_t release()
     {
